@@ -147,11 +147,6 @@ struct Plan {
   size_t partial_floats = 0;
 };
 
-int splits_for(long long P) {
-  long long s = (P + 8191) / 8192;
-  return (int)std::max(1LL, std::min(64LL, s));
-}
-
 Plan make_plan(const lshom_cnn* c, int B, int N, int training) {
   Plan p;
   for (int l = 0, n = N; l < 4; ++l, n /= 3) {
@@ -206,8 +201,8 @@ Plan make_plan(const lshom_cnn* c, int B, int N, int training) {
     for (size_t i = 0; i < c->layers.size(); ++i) {
       const Layer& L = c->layers[i];
       const long long Pout = p.P[lev_of[i]];
-      const size_t rows = (size_t)L.taps * L.cin + 1;
-      pf = std::max(pf, (size_t)splits_for(Pout) * rows * L.np);
+      const int rows = L.taps * L.cin + 1;
+      pf = std::max(pf, (size_t)wgrad_splits(Pout, rows, L.np) * rows * L.np);
     }
     p.partial_floats = pf;
     p.partial = f32((long long)pf);
@@ -302,9 +297,6 @@ hipError_t conv_wgrad(lshom_cnn* c, const Plan& p, const Layer& L, View in, int 
   a.in0 = in.p;
   a.C0 = in.C;
   a.ld0 = in.ld;
-  a.in1 = nullptr;
-  a.C1 = 0;
-  a.ld1 = 0;
   a.B = B;
   a.Hi = a.Wi = Hi;
   a.Ho = a.Wo = Ho;
@@ -316,9 +308,9 @@ hipError_t conv_wgrad(lshom_cnn* c, const Plan& p, const Layer& L, View in, int 
   a.taps = L.taps;
   a.rows = L.taps * L.cin + 1;
   const long long P = (long long)B * Ho * Ho;
-  const int splits = splits_for(P);
+  const int splits = wgrad_splits(P, a.rows, L.np);
   long long pps = (P + splits - 1) / splits;
-  pps = (pps + 31) / 32 * 32;
+  pps = (pps + 127) / 128 * 128;  // whole 32-pixel steps of the four waves
   a.pix_per_split = pps;
   float* partial = at<float>(c, p.partial);
   a.partial = partial;

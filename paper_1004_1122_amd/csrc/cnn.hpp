@@ -43,17 +43,30 @@ struct ConvArgs {
 
 struct WgradArgs {
   const bf16_t* in0;
-  const bf16_t* in1;
-  int C0, C1, ld0, ld1;
+  int C0, ld0;           // input channels (a multiple of 8) and pixel stride
   int B, Hi, Wi, Ho, Wo;
   int mode, up;          // CM_CONV3, CM_DOWN3 or CM_POINT
   const bf16_t* gy;      // [B Ho Wo][ldg], Np channels used
   int ldg, Np;
   int taps;
-  int rows;              // taps (C0 + C1) + 1: the last row sums gy (bias gradient)
+  int rows;              // taps C0 + 1: the last row sums gy (bias gradient)
   long long pix_per_split;
   float* partial;        // [splits][rows][Np]
 };
+
+// Weight-gradient tile of a block: rows of the im2col matrix and output
+// channels (half the accumulators for the 32-channel layers).
+constexpr int kWgradRows = 128;
+inline int wgrad_cols(int Np) { return Np <= 32 ? 32 : 64; }
+// Pixel splits of a layer's weight gradient: about 768 blocks (three per CU,
+// two of which fit at once), each of at least 256 pixels (two steps a wave).
+inline int wgrad_splits(long long pixels, int rows, int Np) {
+  const long long tiles = (long long)((rows + kWgradRows - 1) / kWgradRows) * ((Np + wgrad_cols(Np) - 1) / wgrad_cols(Np));
+  const long long most = (pixels + 255) / 256;
+  long long s = (768 + tiles - 1) / tiles;
+  s = s < most ? s : most;
+  return (int)(s < 256 ? s : 256);
+}
 
 hipError_t launch_conv(const ConvArgs& a, hipStream_t s);
 hipError_t launch_wgrad(const WgradArgs& a, int splits, hipStream_t s);
