@@ -28,6 +28,7 @@ struct Layer {
   int np;         // output channels padded to a multiple of 8
   int taps;
   size_t w_off, b_off;  // offsets (elements) into the parameter arrays
+  size_t f_off, t_off;  // offsets (elements) of the layer's tiles in w16 and wt16
 };
 
 constexpr size_t kAlignEl = 64;  // parameter blocks start on 256-byte boundaries
@@ -45,6 +46,7 @@ struct lshom_cnn {
   int c0 = 32;
   std::vector<Layer> layers;
   size_t n_el = 0;         // elements per parameter array (padded layout)
+  size_t n_f = 0, n_t = 0; // elements of the bfloat16 copies w16 and wt16
   long long n_compact = 0;
   // parameter buffer
   char* pbuf = nullptr;
@@ -123,6 +125,10 @@ void build_layers(lshom_cnn* c) {
     L.b_off = off;
     off = align_el(off + (size_t)L.np);
     compact += (long long)L.taps * L.cin_real * L.cout + L.cout;
+    L.f_off = c->n_f;
+    c->n_f += (size_t)weight_tiles_fwd(L.taps, L.cin, L.np).elements();
+    L.t_off = c->n_t;
+    c->n_t += (size_t)weight_tiles_grad(L.taps, L.cin, L.np, L.kind == K_DOWN3).elements();
   }
   c->n_el = off;
   c->n_compact = compact;
@@ -237,16 +243,15 @@ hipError_t conv_fwd(lshom_cnn* c, const Layer& L, View in, int B, int Hi, int Ho
   a.in0 = in.p;
   a.C0 = in.C;
   a.ld0 = in.ld;
-  a.in1 = nullptr;
-  a.C1 = 0;
-  a.ld1 = 0;
   a.B = B;
   a.Hi = a.Wi = Hi;
   a.Ho = a.Wo = Ho;
   a.mode = mode;
   a.up = up;
-  a.w = c->w16 + L.w_off;
-  a.ldw = L.taps * L.cin;
+  a.w = c->w16 + L.f_off;
+  const WeightTiles wt = weight_tiles_fwd(L.taps, L.cin, L.np);
+  a.wsteps = wt.steps;
+  a.wblocks = wt.blocks;
   a.N = L.cout;
   a.Np = L.np;
   a.bias = c->w + L.b_off;
@@ -255,7 +260,6 @@ hipError_t conv_fwd(lshom_cnn* c, const Layer& L, View in, int B, int Hi, int Ho
   a.ldb = ldb;
   a.out_f = out_f;
   a.ldf = ldf;
-  a.accumulate = 0;
   return launch_conv(a, c->stream);
 }
 
@@ -266,15 +270,16 @@ hipError_t conv_dgrad(lshom_cnn* c, const Layer& L, const bf16_t* gpre, int B, i
   a.C0 = L.np;
   a.ld0 = L.np;
   a.B = B;
-  a.w = c->wt16 + L.w_off;
-  a.ldw = L.taps * L.np;
+  a.w = c->wt16 + L.t_off;
+  const WeightTiles wt = weight_tiles_grad(L.taps, L.cin, L.np, L.kind == K_DOWN3);
+  a.wsteps = wt.steps;
+  a.wblocks = wt.blocks;
   a.N = L.cin;
   a.Np = L.cin;
   a.bias = nullptr;
   a.relu = 0;
   a.out_f = out_f;
   a.ldf = L.cin;
-  a.accumulate = 0;
   if (L.kind == K_CONV3) {
     a.mode = CM_CONV3;
     a.up = 1;
@@ -327,7 +332,7 @@ hipError_t prep(lshom_cnn* c, long long P, int C, int Cp, const float* g0, int l
 hipError_t cast_all(lshom_cnn* c) {
   for (const Layer& L : c->layers) {
     hipError_t e = launch_cast_weights(c->w + L.w_off, L.taps, L.cin, L.np, L.kind == K_CONV3 ? 1 : 0,
-                                       c->w16 + L.w_off, c->wt16 + L.w_off, c->stream);
+                                       L.kind == K_DOWN3 ? 1 : 0, c->w16 + L.f_off, c->wt16 + L.t_off, c->stream);
     if (e != hipSuccess) return e;
     // bias copies are read in FP32; nothing to cast
   }
@@ -575,7 +580,7 @@ const char* lshom_cnn_last_error(const lshom_cnn* c) { return c ? c->err.c_str()
 lshom_status lshom_cnn_param_size(lshom_cnn* c, int64_t* n_params, size_t* buffer_bytes) {
   if (!c) return LSHOM_ERR_INVALID_ARG;
   if (n_params) *n_params = c->n_compact;
-  if (buffer_bytes) *buffer_bytes = c->n_el * (4 * sizeof(float) + 2 * sizeof(bf16_t)) + 256;
+  if (buffer_bytes) *buffer_bytes = c->n_el * 4 * sizeof(float) + (c->n_f + c->n_t) * sizeof(bf16_t) + 256;
   return LSHOM_OK;
 }
 
@@ -597,7 +602,7 @@ lshom_status lshom_cnn_set_param_buffer(lshom_cnn* c, void* dev, size_t bytes) {
   c->v = reinterpret_cast<float*>(q);
   q += c->n_el * 4;
   c->w16 = reinterpret_cast<bf16_t*>(q);
-  q += c->n_el * 2;
+  q += c->n_f * 2;
   c->wt16 = reinterpret_cast<bf16_t*>(q);
   c->params_set = false;
   return LSHOM_OK;
@@ -621,8 +626,6 @@ lshom_status lshom_cnn_set_params(lshom_cnn* c, const float* host, int64_t n) {
   CNN_TRY(c, launch_fill_f32(c->g, (long long)c->n_el, 0.f, c->stream));
   CNN_TRY(c, launch_fill_f32(c->m, (long long)c->n_el, 0.f, c->stream));
   CNN_TRY(c, launch_fill_f32(c->v, (long long)c->n_el, 0.f, c->stream));
-  // the gaps between the layers' bfloat16 copies are never written: clear both copies once
-  CNN_TRY(c, launch_fill_f32(reinterpret_cast<float*>(c->w16), (long long)c->n_el, 0.f, c->stream));
   CNN_TRY(c, cast_all(c));
   CNN_TRY(c, hipStreamSynchronize(c->stream));
   c->adam_t = 0;

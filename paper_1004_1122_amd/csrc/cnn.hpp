@@ -10,6 +10,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "fft_engine.hpp"
+
 namespace lshom {
 namespace cnn {
 
@@ -25,20 +27,20 @@ enum ConvMode : int {
 
 struct ConvArgs {
   const bf16_t* in0;     // channels [0, C0)
-  const bf16_t* in1;     // channels [C0, C0 + C1) (may be null when C1 == 0)
-  int C0, C1, ld0, ld1;  // channel counts (multiples of 8) and pixel strides
+  int C0, ld0;           // channel count and pixel stride (multiples of 8)
   int B, Hi, Wi, Ho, Wo;
   int mode, up;
-  const bf16_t* w;       // element (k, n) of the reduction k < taps (C0 + C1) at w[n * ldw + k]
-                         // (CM_DOWN3_T: slice z starts at w + z * (C0 + C1))
-  int ldw;
+  const bf16_t* w;       // weights in fragment order (WeightTiles): wblocks blocks of 32
+  int wsteps, wblocks;   // output channels, wsteps steps of 32 of the reduction
   int N, Np;             // output channels, padded to a multiple of 8
   const float* bias;     // [N] or null
   int relu;
   bf16_t* out_b;         // bf16 output (or null): pixel stride ldb
   int ldb;
-  float* out_f;          // FP32 output (or null): pixel stride ldf; accumulate adds
-  int ldf, accumulate;
+  float* out_f;          // FP32 output (or null): pixel stride ldf
+  int ldf;
+  int wide_b, wide_f;    // 16-byte stores fit the output's base and stride (set by the launcher)
+  FastDiv fd_chunks;     // C0 / 8 (set by the launcher)
 };
 
 struct WgradArgs {
@@ -95,12 +97,24 @@ hipError_t launch_rel_mse(int B, int N, const float* pred, const double* e, doub
 // the prediction for the transposed image to the load case E = e2.
 // scale 3: the field is 3N x 3N, pixel (i, j) takes prediction (i / 3, j / 3).
 hipError_t launch_make_field(int B, int N, const float* pred, int transpose, int scale, double* e, hipStream_t s);
-// Weight copies, rows contiguous in the reduction index: master w[t][c][o]
-// (taps x cin x np) -> w16[o][t cin + c] for the forward convolution and
-// wt16[c][t' np + o] for the input gradient (conv3 flips the taps, t' = 8 - t;
-// down3 and 1x1 keep them).
-hipError_t launch_cast_weights(const float* w, int taps, int cin, int np, int flip, bf16_t* w16, bf16_t* wt16,
-                               hipStream_t s);
+// A bfloat16 weight operand of the convolutions: `blocks` blocks of 32 rows
+// (output channels of the product), `steps` steps of 32 of its reduction, each
+// step of a half block 1 KB in the matrix cores' fragment order.
+struct WeightTiles {
+  int blocks, steps;
+  long long elements() const { return (long long)blocks * 2 * steps * 512; }
+};
+inline WeightTiles weight_tiles_fwd(int taps, int cin, int np) { return {(np + 31) / 32, (taps * cin + 31) / 32}; }
+// tap_pad: the reduction of every tap padded to whole steps (the input
+// gradient of a stride-3 layer takes one tap per launch slice)
+inline WeightTiles weight_tiles_grad(int taps, int cin, int np, int tap_pad) {
+  return {(cin + 31) / 32, tap_pad ? taps * ((np + 31) / 32) : (taps * np + 31) / 32};
+}
+// Both copies of a layer's master weights w[t][c][o] (taps x cin x np): w16 for
+// the forward convolution, wt16 for the input gradient (conv3 flips the taps,
+// t' = 8 - t; down3 and 1x1 keep them).
+hipError_t launch_cast_weights(const float* w, int taps, int cin, int np, int flip, int tap_pad, bf16_t* w16,
+                               bf16_t* wt16, hipStream_t s);
 hipError_t launch_adam(long long n, float* w, const float* g, float* m, float* v, float lr, float b1, float b2,
                        float eps, float c1, float c2, hipStream_t s);
 hipError_t launch_fill_f32(float* p, long long n, float v, hipStream_t s);

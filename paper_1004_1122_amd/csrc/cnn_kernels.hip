@@ -18,160 +18,375 @@ __device__ __forceinline__ float bf2f(bf16_t h) { return __uint_as_float((uint32
 
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 
-// LDS rows of the tiles hold 32 reduction elements plus 8 of padding (80
-// bytes: 16-byte aligned rows, fewer bank conflicts for the fragment reads).
-constexpr int kTK = 32, kLd = kTK + 8;
+// Implicit-GEMM convolution on the matrix cores (16x16x32 bfloat16 MFMA, FP32
+// accumulation): out[pixel][n] = sum_k im2col(in)[pixel][k] w[n][k], the
+// reduction 32 at a time in the order (tap, channel).
+//
+// A lane's fragment is eight consecutive k of one row of each operand.  The
+// weights are stored in fragment order (1 KB per 16 channels and step, a
+// lane's 16 bytes at 16 lane): read row by row, the 16 lanes of a quarter
+// wave would touch 16 lines a load, and the vector cache's port, not the
+// matrix cores, would set the pace (256 -> 256 channels on 9^2: 27 us by rows).
+// The weights are the first operand: an accumulator then holds channels of
+// one pixel, and the rows of a tile pair are dealt so that a lane ends with
+// eight consecutive channels of its pixel (one 16-byte store).
 
-// Input pixel read by output pixel (b, i, j) at tap t.
-__device__ __forceinline__ long long in_pixel(int mode, int up, int Hi, int Wi, int Ho, int Wo, int b, int i, int j,
-                                              int t) {
-  if (mode == CM_CONV3) {
-    const int p = t / 3, q = t - 3 * (t / 3);
-    int ii = i + p - 1, jj = j + q - 1;
-    ii += ii < 0 ? Ho : 0;
-    ii -= ii >= Ho ? Ho : 0;
-    jj += jj < 0 ? Wo : 0;
-    jj -= jj >= Wo ? Wo : 0;
-    if (up == 3) {
-      ii /= 3;
-      jj /= 3;
-    }
-    return ((long long)b * Hi + ii) * Wi + jj;
-  }
-  if (mode == CM_DOWN3) {
-    const int p = t / 3, q = t - 3 * (t / 3);
-    return ((long long)b * Hi + 3 * i + p) * Wi + 3 * j + q;
-  }
-  return ((long long)b * Hi + i) * Wi + j;
+// The lane's part of step 0 of the weight tile that holds half nt of the
+// channels 32 cb .. 32 cb + 31 (steps 512 elements apart; see cast_weights_kernel).
+__device__ __forceinline__ const bf16_t* conv_weight_tile(const ConvArgs& a, int cb, int nt, int lane) {
+  return a.w + ((long long)(2 * cb + nt) * a.wsteps * 64 + lane) * 8;
 }
 
-// Implicit-GEMM convolution: out[pixel][n] = sum_k im2col(in)[pixel][k] w[k][n]
-// on the matrix cores (16x16x32 bfloat16 MFMA, FP32 accumulation).  A block
-// of 4 waves computes TM = 4 WM output pixels x WN output channels, each
-// wave a WM x WN slab of 16 x 16 tiles.  The reduction runs 32 at a time
-// through two LDS buffers: the global loads of step s + 1 are in flight
-// while step s multiplies, and one block barrier per step separates the
-// writes of one buffer from the reads of the other.  Both operands are
-// K-contiguous (activations: channels of one pixel and tap; weights: rows
-// w[n][k] of ldw elements), so every LDS store and fragment read is 16
-// bytes.  A lane's fragment is eight consecutive k of one row of each
-// operand, the same k for both operands, so the contraction pairs them.
-template <int WM, int WN>
-__global__ __launch_bounds__(256) void conv_kernel(ConvArgs a) {
-  constexpr int TM = 4 * WM, TN = WN, MT = WM / 16, NT = WN / 16;
-  constexpr int A_PER = TM * 4 / 256;                        // uint4 loads of the pixel tile per thread
-  constexpr int B_THREADS = TN * 4;                          // threads loading the weight tile
-  __shared__ __align__(16) bf16_t As[2][TM * kLd];  // [pixel][k]
-  __shared__ __align__(16) bf16_t Bs[2][TN * kLd];  // [channel][k]
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const long long hw = (long long)a.Ho * a.Wo;
-  const long long M = (long long)a.B * hw;
-  const long long m0 = (long long)blockIdx.x * TM;
-  const int n0 = blockIdx.y * TN;
-  const int z = blockIdx.z;
-  const int Cin = a.C0 + a.C1;
-  const int taps = (a.mode == CM_CONV3 || a.mode == CM_DOWN3) ? 9 : 1;
-  const int K = taps * Cin;
-  const bf16_t* W = a.w + (a.mode == CM_DOWN3_T ? (long long)z * Cin : 0);
-
-  // pixel rows (tid / 4) + 64 u of the tile, 8 reduction elements at column 8 (tid % 4)
-  const int kg = tid & 3;
-  int ab[A_PER], ai[A_PER], aj[A_PER];
-  bool av[A_PER];
+// Store channels n .. n + 7 (below a.N) of output pixel op: bias, ReLU, rounding.
+__device__ __forceinline__ void conv_store(const ConvArgs& a, long long op, int n, const float4_t& lo,
+                                           const float4_t& hi, const float (&bias)[8]) {
+  float v[8];
 #pragma unroll
-  for (int u = 0; u < A_PER; ++u) {
-    const long long m = m0 + (tid >> 2) + 64 * u;
-    av[u] = m < M;
-    const long long mm = av[u] ? m : 0;
-    ab[u] = (int)(mm / hw);
-    const int rem = (int)(mm - (long long)ab[u] * hw);
-    ai[u] = rem / a.Wo;
-    aj[u] = rem - ai[u] * a.Wo;
+  for (int e = 0; e < 8; ++e) {
+    v[e] = (e < 4 ? lo[e & 3] : hi[e & 3]) + bias[e];
+    if (a.relu) v[e] = fmaxf(v[e], 0.f);
   }
-  // weight row n0 + tid / 4 (threads below B_THREADS), 8 elements at column 8 (tid % 4)
-  const int bn = n0 + (tid >> 2);
-  const bool bv = tid < B_THREADS && bn < a.Np;
-  const bf16_t* wrow = W + (long long)(bv ? bn : 0) * a.ldw;
-
-  uint4 ra[A_PER], rb = {0u, 0u, 0u, 0u};
-  auto fetch = [&](int k0) {
-    const int k = k0 + 8 * kg;
+  if (a.out_b) {
+    bf16_t* o = a.out_b + op * a.ldb + n;
+    if (n + 8 <= a.N && a.wide_b) {
+      uint4 w;
+      w.x = f2bf(v[0]) | ((uint32_t)f2bf(v[1]) << 16);
+      w.y = f2bf(v[2]) | ((uint32_t)f2bf(v[3]) << 16);
+      w.z = f2bf(v[4]) | ((uint32_t)f2bf(v[5]) << 16);
+      w.w = f2bf(v[6]) | ((uint32_t)f2bf(v[7]) << 16);
+      *reinterpret_cast<uint4*>(o) = w;
+    } else {
 #pragma unroll
-    for (int u = 0; u < A_PER; ++u) {
-      ra[u] = uint4{0u, 0u, 0u, 0u};
-      if (av[u] && k < K) {
-        const int t = k / Cin;
-        const int c = k - t * Cin;
-        const long long pix = in_pixel(a.mode, a.up, a.Hi, a.Wi, a.Ho, a.Wo, ab[u], ai[u], aj[u], t);
-        const bf16_t* src = c < a.C0 ? a.in0 + pix * a.ld0 + c : a.in1 + pix * a.ld1 + (c - a.C0);
-        ra[u] = *reinterpret_cast<const uint4*>(src);
-      }
+      for (int e = 0; e < 8; ++e)
+        if (n + e < a.N) o[e] = f2bf(v[e]);
     }
-    rb = uint4{0u, 0u, 0u, 0u};
-    if (bv && k < K) rb = *reinterpret_cast<const uint4*>(wrow + k);
-  };
-  auto stash = [&](int buf) {
+  }
+  if (a.out_f) {
+    float* o = a.out_f + op * a.ldf + n;
+    if (n + 8 <= a.N && a.wide_f) {
+      *reinterpret_cast<float4_t*>(o) = float4_t{v[0], v[1], v[2], v[3]};
+      *reinterpret_cast<float4_t*>(o + 4) = float4_t{v[4], v[5], v[6], v[7]};
+    } else {
 #pragma unroll
-    for (int u = 0; u < A_PER; ++u)
-      *reinterpret_cast<uint4*>(&As[buf][((tid >> 2) + 64 * u) * kLd + 8 * kg]) = ra[u];
-    if (tid < B_THREADS) *reinterpret_cast<uint4*>(&Bs[buf][(tid >> 2) * kLd + 8 * kg]) = rb;
-  };
+      for (int e = 0; e < 8; ++e)
+        if (n + e < a.N) o[e] = v[e];
+    }
+  }
+}
 
-  float4_t acc[MT][NT];
+// The bias of channels n .. n + 7.
+__device__ __forceinline__ void conv_bias(const ConvArgs& a, int n, float (&bias)[8]) {
+#pragma unroll
+  for (int e = 0; e < 8; ++e) bias[e] = (a.bias && n + e < a.N) ? a.bias[n + e] : 0.f;
+}
+
+// Neighbouring blocks share input rows: one contiguous run of blocks per XCD.
+__device__ __forceinline__ unsigned conv_xcd_block() {
+  const unsigned total = gridDim.x, xcd = blockIdx.x & 7u, slot = blockIdx.x >> 3;
+  const unsigned q = total >> 3, rem = total & 7u;
+  return xcd * q + (xcd < rem ? xcd : rem) + slot;
+}
+
+// Circular 3x3 convolution (CM_CONV3) with the input patch in LDS: a block
+// computes TH x 32 pixels of one image, its (TH + 2) x 34 input pixels staged
+// once with every channel (the nearest-neighbour upsampling of an up layer
+// applied on the way), so that the nine taps read LDS and global memory sees
+// each value about once; read per tap from the vector cache the layer is
+// bound by it (243^2, 32 -> 32 channels: 107 us, whatever the number of loads
+// in flight).  A pixel's row in LDS is its channels and 16 bytes more, which
+// spreads eight consecutive pixels over all banks.  The weights' fragments
+// come straight from global memory, three steps ahead.  A wave owns MT tiles
+// of 16 pixels x 32 channels; with CW = 2 the four waves split 64 channels
+// two ways, so that each weight fragment feeds twice the pixels (81^2, 128 ->
+// 64 channels: 76 -> 50 us).
+// 16 images, the layer alone with both outputs, against two LDS buffers of
+// im2col rows with a block barrier per step: 243^2, 32 -> 32 channels 110 ->
+// 51 us (the FP32 output is 121 MB of its 242); 81^2, 128 -> 64 63 -> 39 us;
+// 27^2, 256 -> 128 54 -> 25 us.  Inference of 16 images 1.40 -> 0.70 ms.
+template <int TH, int CW, bool UNI>
+__global__ __launch_bounds__(256) void conv3_tile_kernel(ConvArgs a) {
+  constexpr int TW = 32, PW = TW + 2, MT = TH * CW / 2, D = 3;
+  extern __shared__ __align__(16) unsigned char patch[];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int li = lane & 15, g = lane >> 4;
+  const int W = a.Wo, H = a.Ho;
+  const int Cin = a.C0, K = 9 * Cin;
+  const int n0 = (int)(blockIdx.y * CW + (CW == 1 ? 0 : wave % CW)) * 32;
+  const unsigned tw = (unsigned)((W + TW - 1) / TW), th = (unsigned)((H + TH - 1) / TH);
+  const unsigned bx = conv_xcd_block();
+  const int b = (int)(bx / (tw * th));
+  const unsigned rem = bx - (unsigned)b * tw * th;
+  const int i0 = (int)(rem / tw) * TH, j0 = (int)(rem % tw) * TW;
+
+  // the weights' first steps, then the patch
+  const bf16_t* wt[2];
+#pragma unroll
+  for (int nt = 0; nt < 2; ++nt) wt[nt] = conv_weight_tile(a, n0 / 32 < a.wblocks ? n0 / 32 : 0, nt, lane);
+  uint4 pw[D][2];
+  const int steps = (K + 31) / 32;
+  auto fetch = [&](int s, int d) {
+#pragma unroll
+    for (int nt = 0; nt < 2; ++nt) pw[d][nt] = *reinterpret_cast<const uint4*>(wt[nt] + 512ll * s);
+  };
+#pragma unroll
+  for (int d = 0; d < D; ++d)
+    if (d < steps) fetch(d, d);
+
+  const int pitch = 2 * Cin + 16;  // bytes of a pixel in the patch
+  {
+    const uint32_t chunks = (uint32_t)Cin / 8u, total = (uint32_t)((TH + 2) * PW) * chunks;
+    const bf16_t* img = a.in0 + (long long)b * a.Hi * a.Wi * a.ld0;
+    constexpr int kIn = 6;  // loads in flight per thread
+    for (uint32_t e0 = tid; e0 < total; e0 += 256 * kIn) {
+      uint4 v[kIn];
+      uint32_t at[kIn];
+#pragma unroll
+      for (int u = 0; u < kIn; ++u) {
+        const uint32_t e = e0 + 256u * u;
+        const uint32_t px = fdiv(e, a.fd_chunks), c = e - px * chunks;
+        const int hy = (int)(px / PW), hx = (int)(px - (px / PW) * PW);
+        // circular; beyond the image's end any pixel serves (not stored)
+        int ii = i0 + hy - 1, jj = j0 + hx - 1;
+        ii += ii < 0 ? H : 0;
+        ii -= ii >= H ? H : 0;
+        jj += jj < 0 ? W : 0;
+        jj -= jj >= W ? W : 0;
+        if (a.up == 3) {
+          ii = (int)((uint32_t)ii / 3u);
+          jj = (int)((uint32_t)jj / 3u);
+        }
+        at[u] = px * (uint32_t)pitch + c * 16u;
+        v[u] = uint4{0u, 0u, 0u, 0u};
+        if (e < total) v[u] = *reinterpret_cast<const uint4*>(img + ((long long)ii * a.Wi + jj) * a.ld0 + 8 * c);
+      }
+#pragma unroll
+      for (int u = 0; u < kIn; ++u)
+        if (e0 + 256u * u < total) *reinterpret_cast<uint4*>(patch + at[u]) = v[u];
+    }
+  }
+  __syncthreads();
+
+  // tile T = (wave / CW) MT + mt: row T / 2, columns 16 (T % 2) ..
+  const unsigned char* px0[MT];
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt) {
+    const int T = (wave / CW) * MT + mt;
+    px0[mt] = patch + ((T >> 1) * PW + 16 * (T & 1) + li) * pitch + (UNI ? 16 * g : 0);
+  }
+  float4_t acc[MT][2];
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = float4_t{0.f, 0.f, 0.f, 0.f};
-
-  fetch(0);
-  stash(0);
-  __syncthreads();
-  const int steps = (K + kTK - 1) / kTK;
-  for (int s = 0; s < steps; ++s) {
-    const int cur = s & 1;
-    if (s + 1 < steps) fetch((s + 1) * kTK);
-    bf16x8_t af[MT], bfr[NT];
+    for (int nt = 0; nt < 2; ++nt) acc[mt][nt] = float4_t{0.f, 0.f, 0.f, 0.f};
+  int tap = 0, off = 0, cc = 0;  // UNI: byte offset of the step's tap and channels
+  for (int s0 = 0; s0 < steps; s0 += D) {
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-      af[mt] = *reinterpret_cast<const bf16x8_t*>(&As[cur][(wave * WM + mt * 16 + (lane & 15)) * kLd + 8 * (lane >> 4)]);
+    for (int d = 0; d < D; ++d) {
+      const int s = s0 + d;
+      if (s >= steps) break;
+      bf16x8_t fa[MT];
+      if constexpr (UNI) {
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt)
-      bfr[nt] = *reinterpret_cast<const bf16x8_t*>(&Bs[cur][(nt * 16 + (lane & 15)) * kLd + 8 * (lane >> 4)]);
+        for (int mt = 0; mt < MT; ++mt) fa[mt] = *reinterpret_cast<const bf16x8_t*>(px0[mt] + off + 2 * cc);
+        cc += 32;
+        if (cc == Cin) {
+          cc = 0;
+          ++tap;
+          off = ((tap / 3) * PW + tap % 3) * pitch;
+        }
+      } else {
+        const int k = 32 * s + 8 * g;
+        const bool in = k < K;
+        const int t = in ? k / Cin : 0, c = in ? k - t * Cin : 0;
+        const int o = ((t / 3) * PW + t % 3) * pitch + 2 * c;
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
+        for (int mt = 0; mt < MT; ++mt) {
+          const uint4 v = *reinterpret_cast<const uint4*>(px0[mt] + o);
+          fa[mt] = __builtin_bit_cast(bf16x8_t, in ? v : uint4{0u, 0u, 0u, 0u});
+        }
+      }
 #pragma unroll
-      for (int nt = 0; nt < NT; ++nt)
-        acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[mt], bfr[nt], acc[mt][nt], 0, 0, 0);
-    if (s + 1 < steps) stash(cur ^ 1);
-    __syncthreads();
+      for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int nt = 0; nt < 2; ++nt)
+          acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, pw[d][nt]), fa[mt],
+                                                                acc[mt][nt], 0, 0, 0);
+      if (s + D < steps) fetch(s + D, d);
+    }
   }
 
+  const int n = n0 + 8 * g;
+  if (n >= a.N) return;
+  float bias[8];
+  conv_bias(a, n, bias);
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt) {
+    const int T = (wave / CW) * MT + mt;
+    const int i = i0 + (T >> 1), j = j0 + 16 * (T & 1) + li;
+    if (i >= H || j >= W) continue;
+    conv_store(a, ((long long)b * H + i) * W + j, n, acc[mt][0], acc[mt][1], bias);
+  }
+}
+
+// The other convolutions (stride-3, its transpose, 1x1: every input value is
+// used by one tap) and the 3x3 ones of small images: every fragment straight
+// from global memory, no LDS and no barrier.  A wave computes 16 MT pixels x
+// 32 NP channels; the loads of the next D steps are in flight while a step
+// multiplies.
+//
+// UNI: the input channels are a multiple of 32, so a step lies in one tap for
+// all lanes; otherwise each lane finds the tap of its eight k.
+template <int MT, int NP, int TAPS, bool UNI, int D>
+__global__ __launch_bounds__(256) void conv_kernel(ConvArgs a) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int li = lane & 15, g = lane >> 4;
+  const unsigned bx = conv_xcd_block();
+  const int W = a.Wo, H = a.Ho;
+  const int hw = H * W;
+  const int M = a.B * hw;  // below 2^25
+  const int m0 = (int)(bx * 4 + wave) * (16 * MT);
+  if (m0 >= M) return;
+  const int n0 = blockIdx.y * (32 * NP);
+  const int z = blockIdx.z;
+  const int Cin = a.C0;
+  const int K = TAPS * Cin;
+  const uint32_t ld8 = (uint32_t)a.ld0 / 8u;
+
+  // first pixel (in units of 8 elements) of the input rows, and the input
+  // columns, of the taps of the lane's pixel in each tile
+  uint32_t rowoff[MT][TAPS == 9 ? 3 : 1], coloff[MT][TAPS == 9 ? 3 : 1];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const long long m = m0 + wave * WM + mt * 16 + 4 * (lane >> 4) + i;
+  for (int mt = 0; mt < MT; ++mt) {
+    int m = m0 + 16 * mt + li;
+    m = m < M ? m : M - 1;  // rows past the end are computed and not stored
+    const int b = m / hw, rem = m - b * hw;
+    const int i = rem / W, j = rem - i * W;
+    if constexpr (TAPS == 9) {
+#pragma unroll
+      for (int t = 0; t < 3; ++t) {
+        int ii = 3 * i + t, jj = 3 * j + t;
+        if (a.mode == CM_CONV3) {
+          ii = i + t - 1;
+          ii += ii < 0 ? H : 0;
+          ii -= ii >= H ? H : 0;
+          jj = j + t - 1;
+          jj += jj < 0 ? W : 0;
+          jj -= jj >= W ? W : 0;
+          if (a.up == 3) {
+            ii = (int)((uint32_t)ii / 3u);
+            jj = (int)((uint32_t)jj / 3u);
+          }
+        }
+        rowoff[mt][t] = (uint32_t)(b * a.Hi + ii) * (uint32_t)a.Wi * ld8;
+        coloff[mt][t] = (uint32_t)jj * ld8;
+      }
+    } else {
+      rowoff[mt][0] = (uint32_t)(b * a.Hi + i) * (uint32_t)a.Wi * ld8;
+      coloff[mt][0] = (uint32_t)j * ld8;
+    }
+  }
+  const bf16_t* wt[2 * NP];
+#pragma unroll
+  for (int nt = 0; nt < 2 * NP; ++nt) {
+    const int cb = n0 / 32 + (nt >> 1);
+    wt[nt] = conv_weight_tile(a, cb < a.wblocks ? cb : 0, nt & 1, lane) +
+             (a.mode == CM_DOWN3_T ? (long long)z * ((Cin + 31) / 32) * 512 : 0);
+  }
+
+  // (values first: a conditional on the array elements themselves would index the arrays in scratch memory)
+  auto tap_pixel = [&](int mt, int p, int q) -> uint32_t {
+    if constexpr (TAPS == 9) {
+      const uint32_t r0 = rowoff[mt][0], r1 = rowoff[mt][1], r2 = rowoff[mt][2];
+      const uint32_t c0 = coloff[mt][0], c1 = coloff[mt][1], c2 = coloff[mt][2];
+      return (p == 0 ? r0 : (p == 1 ? r1 : r2)) + (q == 0 ? c0 : (q == 1 ? c1 : c2));
+    } else {
+      return rowoff[mt][0] + coloff[mt][0];
+    }
+  };
+  uint4 pa[D][MT], pw[D][2 * NP];
+  const bf16_t* src[MT];  // the lane's eight channels of the fetch position (UNI)
+  int fp = 0, fq = 0, fc = 0;
+  auto tap_source = [&]() {
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {
+      src[mt] = a.in0 + 8ull * tap_pixel(mt, fp, fq) + 8 * g;
+    }
+  };
+  if constexpr (UNI) tap_source();
+  auto fetch = [&](int s, int d) {
+    if constexpr (UNI) {
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) pa[d][mt] = *reinterpret_cast<const uint4*>(src[mt] + fc);
+#pragma unroll
+      for (int nt = 0; nt < 2 * NP; ++nt) pw[d][nt] = *reinterpret_cast<const uint4*>(wt[nt] + 512ll * s);
+      fc += 32;
+      if (fc == Cin) {
+        fc = 0;
+        if (++fq == 3) {
+          fq = 0;
+          ++fp;
+        }
+        if (fp < 3) tap_source();
+      }
+    } else {
+      const int k = 32 * s + 8 * g;
+      const bool in = k < K;
+      const int t = in ? k / Cin : 0, c = in ? k - t * Cin : 0;
+      const int p = TAPS == 9 ? t / 3 : 0, q = TAPS == 9 ? t - 3 * p : 0;
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) {
+        const uint4 v = *reinterpret_cast<const uint4*>(a.in0 + 8ull * tap_pixel(mt, p, q) + c);
+        pa[d][mt] = in ? v : uint4{0u, 0u, 0u, 0u};
+      }
+#pragma unroll
+      for (int nt = 0; nt < 2 * NP; ++nt) pw[d][nt] = *reinterpret_cast<const uint4*>(wt[nt] + 512ll * s);
+    }
+  };
+
+  float4_t acc[MT][2 * NP];
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+    for (int nt = 0; nt < 2 * NP; ++nt) acc[mt][nt] = float4_t{0.f, 0.f, 0.f, 0.f};
+  const int steps = (K + 31) / 32;
+#pragma unroll
+  for (int d = 0; d < D; ++d)
+    if (d < steps) fetch(d, d);
+  for (int s0 = 0; s0 < steps; s0 += D) {
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+      const int s = s0 + d;
+      if (s >= steps) break;
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int nt = 0; nt < 2 * NP; ++nt)
+          acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, pw[d][nt]),
+                                                                __builtin_bit_cast(bf16x8_t, pa[d][mt]), acc[mt][nt],
+                                                                0, 0, 0);
+      if (s + D < steps) fetch(s + D, d);
+    }
+  }
+
+  // lane (li, g): pixel li of the tile, channels n0 + 32 pr + 8 g + (0..7)
+#pragma unroll
+  for (int pr = 0; pr < NP; ++pr) {
+    const int n = n0 + 32 * pr + 8 * g;
+    if (n >= a.N) continue;
+    float bias[8];
+    conv_bias(a, n, bias);
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {
+      const int m = m0 + 16 * mt + li;
       if (m >= M) continue;
       long long op = m;
       if (a.mode == CM_DOWN3_T) {
-        const int b = (int)(m / hw);
-        const int rem = (int)(m - (long long)b * hw);
-        const int ii = rem / a.Wo, jj = rem - (rem / a.Wo) * a.Wo;
+        const int b = m / hw, rem = m - b * hw;
+        const int ii = rem / W, jj = rem - ii * W;
         const int p = z / 3, q = z - 3 * (z / 3);
-        op = ((long long)b * 3 * a.Ho + 3 * ii + p) * (3LL * a.Wo) + 3 * jj + q;
+        op = ((long long)b * 3 * H + 3 * ii + p) * (3LL * W) + 3 * jj + q;
       }
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt) {
-        const int n = n0 + nt * 16 + (lane & 15);
-        if (n >= a.N) continue;
-        float v = acc[mt][nt][i] + (a.bias ? a.bias[n] : 0.f);
-        if (a.relu) v = fmaxf(v, 0.f);
-        if (a.out_b) a.out_b[op * a.ldb + n] = f2bf(v);
-        if (a.out_f) {
-          float* d = a.out_f + op * a.ldf + n;
-          *d = a.accumulate ? *d + v : v;
-        }
-      }
+      conv_store(a, op, n, acc[mt][2 * pr], acc[mt][2 * pr + 1], bias);
     }
   }
 }
@@ -606,18 +821,35 @@ __global__ void make_field_kernel(int B, int N, const float* pred, int transpose
   }
 }
 
-__global__ void cast_weights_kernel(const float* w, int taps, int cin, int np, int flip, bf16_t* w16, bf16_t* wt16) {
-  const long long n = (long long)taps * cin * np;
-  for (long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (long long)gridDim.x * blockDim.x) {
-    const int o = (int)(e % np);
-    const long long t2 = e / np;
-    const int c = (int)(t2 % cin);
-    const int t = (int)(t2 / cin);
-    const bf16_t h = f2bf(w[e]);
-    // forward: row o, k = t cin + c; input gradient: row c, k = t' np + o
-    w16[(long long)o * taps * cin + t2] = h;
-    const int tt = flip ? taps - 1 - t : t;
-    wt16[((long long)c * taps + tt) * np + o] = h;
+// Fragment order of a weight operand: element e of lane l of step s of tile
+// t (16 channels: half t % 2 of the 32 of block t / 2) at ((t S + s) 64 + l) 8
+// + e is row 32 (t / 2) + 8 (li / 4) + 4 (t % 2) + li % 4 (li = l % 16),
+// reduction index 32 s + 8 (l / 16) + e; zeros beyond the operand's rows and
+// reduction.  Forward: row o, k = t cin + c.  Input gradient: row c,
+// k = t' np + o, each tap's np padded to whole steps for a stride-3 layer
+// (whose launches take one tap each).
+__global__ void cast_weights_kernel(const float* w, int taps, int cin, int np, int flip, int tap_pad, int steps_f,
+                                    long long n_f, int steps_t, long long n_t, bf16_t* w16, bf16_t* wt16) {
+  for (long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x; e < n_f + n_t;
+       e += (long long)gridDim.x * blockDim.x) {
+    const bool fwd = e < n_f;
+    const long long q = fwd ? e : e - n_f;
+    const int l = (int)(q >> 3) & 63, li = l & 15;
+    const int ts = (int)(q >> 9), S = fwd ? steps_f : steps_t;
+    const int t2 = ts / S, s = ts - t2 * S;
+    const int row = 32 * (t2 >> 1) + 8 * (li >> 2) + 4 * (t2 & 1) + (li & 3);
+    const int k = 32 * s + 8 * (l >> 4) + (int)(q & 7);
+    float v = 0.f;
+    if (fwd) {
+      if (row < np && k < taps * cin) v = w[(long long)k * np + row];
+      w16[q] = f2bf(v);
+    } else {
+      const int per = tap_pad ? (np + 31) / 32 * 32 : np;
+      const int tt = k / per, o = k - tt * per;
+      const int t = flip ? taps - 1 - tt : tt;
+      if (row < cin && tt < taps && o < np) v = w[((long long)t * cin + row) * np + o];
+      wt16[q] = f2bf(v);
+    }
   }
 }
 
@@ -642,25 +874,69 @@ __global__ void fill_f32_kernel(float* p, long long n, float v) {
 // Launchers
 // ---------------------------------------------------------------------------
 
+constexpr long long kConvWaves = 1536;  // waves of a direct launch (two per SIMD on three SIMDs of four)
+// Image side from which the LDS patch pays: below, a 32-pixel row of a tile
+// is mostly past the image's end.
+constexpr int kConvTileSide = 27;
+constexpr size_t kConvTileLds8 = 60 * 1024, kConvTileLds4 = 120 * 1024;
+static size_t conv3_tile_lds(int th, int cin) { return (size_t)(th + 2) * 34 * (2 * cin + 16); }
+
 static unsigned grid_for(long long n, int per = 256, long long cap = 8192) {
   long long b = (n + per - 1) / per;
   if (b < 1) b = 1;
   return (unsigned)(b > cap ? cap : b);
 }
 
-hipError_t launch_conv(const ConvArgs& a, hipStream_t s) {
+template <int MT, int NP, int D>
+static hipError_t launch_conv_tile(const ConvArgs& a, hipStream_t s) {
   const long long M = (long long)a.B * a.Ho * a.Wo;
-  const unsigned zs = a.mode == CM_DOWN3_T ? 9 : 1;
-  // channel tile sized to the layer (32 or 64 columns; 32 x 32 wave slabs
-  // beat 64 x 32 ones on the 32-channel layers: more blocks per CU)
-  if (a.Np <= 32) {
-    hipLaunchKernelGGL((conv_kernel<32, 32>), dim3((unsigned)((M + 127) / 128), (unsigned)((a.Np + 31) / 32), zs),
-                       dim3(256), 0, s, a);
-  } else {
-    hipLaunchKernelGGL((conv_kernel<32, 64>), dim3((unsigned)((M + 127) / 128), (unsigned)((a.Np + 63) / 64), zs),
-                       dim3(256), 0, s, a);
-  }
+  const bool nine = a.mode == CM_CONV3 || a.mode == CM_DOWN3, uni = a.C0 % 32 == 0;
+  const dim3 grid((unsigned)((M + 64 * MT - 1) / (64 * MT)), (unsigned)((a.N + 32 * NP - 1) / (32 * NP)),
+                  a.mode == CM_DOWN3_T ? 9u : 1u);
+  if (nine && uni) hipLaunchKernelGGL((conv_kernel<MT, NP, 9, true, D>), grid, dim3(256), 0, s, a);
+  else if (nine) hipLaunchKernelGGL((conv_kernel<MT, NP, 9, false, D>), grid, dim3(256), 0, s, a);
+  else if (uni) hipLaunchKernelGGL((conv_kernel<MT, NP, 1, true, D>), grid, dim3(256), 0, s, a);
+  else hipLaunchKernelGGL((conv_kernel<MT, NP, 1, false, D>), grid, dim3(256), 0, s, a);
   return hipGetLastError();
+}
+
+template <int TH, int CW>
+static hipError_t launch_conv3_tile(const ConvArgs& a, hipStream_t s) {
+  const dim3 grid((unsigned)((long long)a.B * ((a.Ho + TH - 1) / TH) * ((a.Wo + 31) / 32)),
+                  (unsigned)((a.Np + 32 * CW - 1) / (32 * CW)));
+  const size_t lds = conv3_tile_lds(TH, a.C0);
+  if (a.C0 % 32 == 0) hipLaunchKernelGGL((conv3_tile_kernel<TH, CW, true>), grid, dim3(256), lds, s, a);
+  else hipLaunchKernelGGL((conv3_tile_kernel<TH, CW, false>), grid, dim3(256), lds, s, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_conv(const ConvArgs& in, hipStream_t s) {
+  ConvArgs a = in;
+  a.wide_b = a.ldb % 8 == 0 && (reinterpret_cast<uintptr_t>(a.out_b) & 15u) == 0;
+  a.wide_f = a.ldf % 4 == 0 && (reinterpret_cast<uintptr_t>(a.out_f) & 15u) == 0;
+  a.fd_chunks = make_fastdiv((uint32_t)a.C0 / 8u);
+  if (a.mode == CM_CONV3 && a.Wo >= kConvTileSide) {
+    // eight rows a block while two blocks fit a CU (the patch's two extra rows
+    // weigh less: 64 -> 32 channels on 243^2 87 us, four rows 102 us), else
+    // four rows; wider layers (over 270 channels) read global memory per tap
+    if (conv3_tile_lds(8, a.C0) <= kConvTileLds8)
+      return a.N <= 32 ? launch_conv3_tile<8, 1>(a, s) : launch_conv3_tile<8, 2>(a, s);
+    if (conv3_tile_lds(4, a.C0) <= kConvTileLds4)
+      return a.N <= 32 ? launch_conv3_tile<4, 1>(a, s) : launch_conv3_tile<4, 2>(a, s);
+  }
+  // the largest wave tile that still gives two waves to most SIMDs; below
+  // that a layer is bound by the length of its reduction, and narrow tiles
+  // with more steps in flight win
+  const long long M = (long long)a.B * a.Ho * a.Wo * (a.mode == CM_DOWN3_T ? 9 : 1);
+  auto waves = [&](int mt, int np) { return ((M + 16 * mt - 1) / (16 * mt)) * ((a.Np + 32 * np - 1) / (32 * np)); };
+  if (a.Np > 32) {
+    if (waves(4, 2) >= kConvWaves) return launch_conv_tile<4, 2, 2>(a, s);
+    if (waves(2, 2) >= kConvWaves) return launch_conv_tile<2, 2, 3>(a, s);
+  } else if (waves(4, 1) >= kConvWaves) {
+    return launch_conv_tile<4, 1, 3>(a, s);
+  }
+  if (waves(2, 1) >= kConvWaves) return launch_conv_tile<2, 1, 4>(a, s);
+  return launch_conv_tile<1, 1, 6>(a, s);
 }
 
 hipError_t launch_wgrad(const WgradArgs& a, int splits, hipStream_t s) {
@@ -718,10 +994,11 @@ hipError_t launch_make_field(int B, int N, const float* pred, int transpose, int
   return hipGetLastError();
 }
 
-hipError_t launch_cast_weights(const float* w, int taps, int cin, int np, int flip, bf16_t* w16, bf16_t* wt16,
-                               hipStream_t s) {
-  hipLaunchKernelGGL(cast_weights_kernel, dim3(grid_for((long long)taps * cin * np)), dim3(256), 0, s, w, taps, cin,
-                     np, flip, w16, wt16);
+hipError_t launch_cast_weights(const float* w, int taps, int cin, int np, int flip, int tap_pad, bf16_t* w16,
+                               bf16_t* wt16, hipStream_t s) {
+  const WeightTiles f = weight_tiles_fwd(taps, cin, np), t = weight_tiles_grad(taps, cin, np, tap_pad);
+  hipLaunchKernelGGL(cast_weights_kernel, dim3(grid_for(f.elements() + t.elements())), dim3(256), 0, s, w, taps, cin,
+                     np, flip, tap_pad, f.steps, f.elements(), t.steps, t.elements(), w16, wt16);
   return hipGetLastError();
 }
 
