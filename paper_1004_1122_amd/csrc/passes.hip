@@ -29,6 +29,8 @@
 // for L0 = l0 I, s = 1 and lbar = l0.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "kernels.hpp"
 #include "reduce.hpp"
 
@@ -1426,9 +1428,22 @@ long long update_blocks(long long n) {
   return b > kUpdateBlocks ? kUpdateBlocks : (b < 1 ? 1 : b);
 }
 
-// Block size: 128 threads when the batch fits their butterfly capacity.
-static int pick_threads(int points, const FftPlan& plan) {
-  return points <= plan_batch_cap(plan, 128) ? 128 : 256;
+// Block size: two waves where they hold the butterflies.  Four where more
+// than 128 butterflies of a heavy radix would give two waves a second round
+// that leaves one of them idle and LDS holds at most four blocks per CU, so
+// that there are too few waves to fill in (729^2, 162 butterflies of radix 9,
+// 38 KB: 22.9 / 28.6 / 21.5 us for the three passes with two waves, 18.2 /
+// 23.6 / 16.5 us with four; ten such problems 79 / 122 / 79 us and 63 / 96 / 62
+// us); with more blocks per CU two waves are the better (32 problems of 243^2
+// FP32, 3.9 KB: 15.2 us, with four 17.5 us).  The choice depends on the grid
+// alone, as it sets the order of the sums and a batch reproduces single
+// solves bit for bit.
+static int pick_threads(int points, const FftPlan& plan, size_t lds) {
+  if (points > plan_batch_cap(plan, 128)) return 256;
+  int heavy = 0;
+  for (int s = 0; s < plan.nstages; ++s)
+    if (plan.radix[s] >= 5) heavy = std::max(heavy, points / plan.radix[s]);
+  return heavy > 128 && 5 * lds > 160 * 1024 ? 256 : 128;
 }
 
 // Largest phase index of a phase image (validation at workspace set-up).
@@ -1505,7 +1520,7 @@ hipError_t launch_row(const RowArgs<T>& a, hipStream_t s) {
   const int comps = a.split ? 1 : a.d;
   const size_t lds = row_lds_bytes(a.n, a.rows_per_block, comps, (int)sizeof(cx<T>), a.n_phases, nullptr);
   const long long nb = row_blocks(a);
-  const int nt = a.nt ? a.nt : pick_threads(comps * (a.rows_per_block / 2) * a.n, a.plan);
+  const int nt = a.nt ? a.nt : pick_threads(comps * (a.rows_per_block / 2) * a.n, a.plan, lds);
   switch (plan_radix_set(a.plan)) {
     case RADIX_POW3: launch_row_rs<T, RADIX_POW3>(a, lds, nb, nt, s); break;
     case RADIX_POW2: launch_row_rs<T, RADIX_POW2>(a, lds, nb, nt, s); break;
@@ -1519,7 +1534,7 @@ template <typename T>
 hipError_t launch_col(const ColArgs<T>& a, hipStream_t s) {
   const size_t lds = col_lds_bytes(a.L, a.tile, a.d, (int)sizeof(cx<T>), nullptr);
   const long long nb = col_blocks(a);
-  const int nt = a.nt ? a.nt : pick_threads(a.d * a.tile * a.L, a.plan);
+  const int nt = a.nt ? a.nt : pick_threads(a.d * a.tile * a.L, a.plan, lds);
   switch (plan_radix_set(a.plan)) {
     case RADIX_POW3: launch_col_rs<T, RADIX_POW3>(a, lds, nb, nt, s); break;
     case RADIX_POW2: launch_col_rs<T, RADIX_POW2>(a, lds, nb, nt, s); break;
