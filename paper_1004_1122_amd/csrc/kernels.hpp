@@ -460,6 +460,26 @@ __host__ __device__ inline long long w3_entries(long long N0, long long N1, long
   return N0 * N1 * (long long)w3_groups((int)(N2 / 2 + 1)) * kW3Group;
 }
 
+// ---------------------------------------------------------------------------
+// Passes of 2-D grids along axes of 81, 243 or 729 nodes (wave2d.hip): the
+// same reads and writes as the block passes (transposed layout), chosen per
+// axis by launch_row and launch_col.  27 nodes stay with the block passes: a
+// launch is pure latency there (10 us either way), and mixed solves of 27^2
+// images at contrasts of 1e4 and more, whose iterations outnumber the
+// unknowns, converge or stall by their rounding.
+// ---------------------------------------------------------------------------
+__host__ __device__ constexpr bool w2_length(long long n) { return n == 81 || n == 243 || n == 729; }
+// scalar phases; every row mode
+template <typename T>
+bool w2_row(const RowArgs<T>& a) { return a.d == 2 && a.row_fast && !a.tensor && w2_length(a.n); }
+// isotropic reference; the pipelined-CG forms of these passes stay block passes
+template <typename T>
+bool w2_col(const ColArgs<T>& a) { return a.dims == 2 && a.sl == 1 && !a.aniso && w2_length(a.L); }
+// sequences (row pairs, columns) of one block
+int w2_seqs(int n);
+template <typename T> hipError_t launch_w2_row(const RowArgs<T>& a, hipStream_t s);
+template <typename T> hipError_t launch_w2_col(const ColArgs<T>& a, hipStream_t s);
+
 // Host launchers (passes.hip).
 template <typename T> hipError_t launch_row(const RowArgs<T>& a, hipStream_t s);
 template <typename T> hipError_t launch_col(const ColArgs<T>& a, hipStream_t s);
@@ -485,6 +505,7 @@ hipError_t launch_max_phase(const uint8_t* ph, long long n, unsigned* out, hipSt
 // counts[0..256): nodes of each phase index (counts zero on entry)
 hipError_t launch_phase_histogram(const uint8_t* ph, long long n, unsigned* counts, hipStream_t s);
 
+// partial sums per problem: of ROW_INV with ROWF_LEFF (three each), of COL_FWD_PROJ with a dot
 template <typename T> long long row_blocks(const RowArgs<T>& a);
 template <typename T> long long col_blocks(const ColArgs<T>& a);
 long long update_blocks(long long n);

@@ -1415,11 +1415,13 @@ size_t col_lds_bytes(int L, int tile, int d, int elem_bytes, int* ss_out) {
 
 template <typename T>
 long long row_blocks(const RowArgs<T>& a) {
+  if (w2_row(a)) return (a.nrows + 2 * w2_seqs(a.n) - 1) / (2 * w2_seqs(a.n));
   return (a.split ? a.d : 1) * ((a.nrows + a.rows_per_block - 1) / a.rows_per_block);
 }
 
 template <typename T>
 long long col_blocks(const ColArgs<T>& a) {
+  if (w2_col(a) && !a.pipe) return (a.inner + w2_seqs(a.L) - 1) / w2_seqs(a.L);
   return a.outer * (long long)a.tiles_per_outer;
 }
 
@@ -1517,6 +1519,7 @@ static void launch_col_rs(const ColArgs<T>& a, size_t lds, long long nb, int nt,
 
 template <typename T>
 hipError_t launch_row(const RowArgs<T>& a, hipStream_t s) {
+  if (w2_row(a)) return launch_w2_row(a, s);
   const int comps = a.split ? 1 : a.d;
   const size_t lds = row_lds_bytes(a.n, a.rows_per_block, comps, (int)sizeof(cx<T>), a.n_phases, nullptr);
   const long long nb = row_blocks(a);
@@ -1532,6 +1535,7 @@ hipError_t launch_row(const RowArgs<T>& a, hipStream_t s) {
 
 template <typename T>
 hipError_t launch_col(const ColArgs<T>& a, hipStream_t s) {
+  if (w2_col(a) && !a.pipe && (a.mode == COL_INV_C || a.mode == COL_FWD_PROJ)) return launch_w2_col(a, s);
   const size_t lds = col_lds_bytes(a.L, a.tile, a.d, (int)sizeof(cx<T>), nullptr);
   const long long nb = col_blocks(a);
   const int nt = a.nt ? a.nt : pick_threads(a.d * a.tile * a.L, a.plan, lds);

@@ -1,4 +1,5 @@
-// Wave-level FFTs of length N = 9^m 3^e <= 243 for gfx950.
+// Wave-level FFTs of length N = 9^m 3^e <= 243 for gfx950, and the same
+// transform of 729 points by the lanes of a block.
 //
 // One sequence of N complex points is owned by LPS = N / 9 lanes of a
 // wavefront, each lane holding 9 points; a wave holds SPW = 64 / LPS
@@ -9,6 +10,10 @@
 // all nine values of the lane's butterfly), LDS executes a wave's
 // instructions in order, and a wave barrier keeps the compiler from moving
 // memory operations across a stage boundary.
+//
+// 729 points have 81 lanes, more than a wave: the sequences of a block then
+// exchange between block barriers in the same places (every thread of the
+// block takes part in the calls).
 //
 // Stage with radix R and Ns = product of the radices before it: job q
 // (q < N / R) reads x[q + r N / R], multiplies by W_{Ns R}^{r k} with
@@ -25,10 +30,17 @@ namespace lshom {
 
 template <int N>
 struct WaveGeom {
-  static_assert(N == 9 || N == 27 || N == 81 || N == 243, "wave FFT lengths: 9, 27, 81, 243");
+  static_assert(N == 9 || N == 27 || N == 81 || N == 243 || N == 729, "wave FFT lengths: 9, 27, 81, 243, 729");
   static constexpr int LPS = N / 9;         // lanes per sequence
-  static constexpr int SPW = 64 / LPS;      // sequences per wave
+  static constexpr int SPW = 64 / LPS;      // sequences per wave (729: none)
 };
+
+// Order the exchanges of a stage: within the wave, or (729) within the block.
+template <int N>
+__device__ __forceinline__ void fft_sync() {
+  if constexpr (N > 243) __syncthreads();
+  else __builtin_amdgcn_wave_barrier();
+}
 
 namespace wfft_detail {
 
@@ -62,7 +74,7 @@ __device__ __forceinline__ void stages_from(cx<T>* buf, const cx<T>* __restrict_
         v[r] = cmul(v[r], w);
       }
     }
-    __builtin_amdgcn_wave_barrier();
+    fft_sync<N>();
     if constexpr (KEEP && M == R) {
       // last stage (one job per lane, q = j = k): x[j + r N / 9]
       if (act) {
@@ -76,7 +88,7 @@ __device__ __forceinline__ void stages_from(cx<T>* buf, const cx<T>* __restrict_
 #pragma unroll
         for (int r = 0; r < R; ++r) buf[(j - k) * R + k + r * NS] = v[r];
       }
-      __builtin_amdgcn_wave_barrier();
+      fft_sync<N>();
       stages_from<T, N, S, NS * R, KEEP>(buf, tw, j, act, out);
     }
   } else {
@@ -100,7 +112,7 @@ __device__ __forceinline__ void stages_from(cx<T>* buf, const cx<T>* __restrict_
         }
       }
     }
-    __builtin_amdgcn_wave_barrier();
+    fft_sync<N>();
     if constexpr (KEEP) {
       // jobs q = j + LPS t (k = q): x[j + LPS (t + 3 r)]
       (void)kk;
@@ -121,7 +133,7 @@ __device__ __forceinline__ void stages_from(cx<T>* buf, const cx<T>* __restrict_
           for (int r = 0; r < R; ++r) buf[kk[t] + r * NS] = u[t][r];
         }
       }
-      __builtin_amdgcn_wave_barrier();
+      fft_sync<N>();
     }
   }
 }
@@ -138,13 +150,13 @@ template <typename T, int N, int S>
 __device__ __forceinline__ void wave_fft(cx<T> (&v)[9], cx<T>* buf, const cx<T>* __restrict__ tw, int j,
                                          bool act) {
   // first stage: radix 9, Ns = 1 (no twiddles): writes x[9 j + r]
-  __builtin_amdgcn_wave_barrier();
+  fft_sync<N>();
   if (act) {
     dft<T, 9, S>(v);
 #pragma unroll
     for (int r = 0; r < 9; ++r) buf[9 * j + r] = v[r];
   }
-  __builtin_amdgcn_wave_barrier();
+  fft_sync<N>();
   wfft_detail::stages_from<T, N, S, 9>(buf, tw, j, act);
 }
 
@@ -154,7 +166,7 @@ template <typename T, int N, int S>
 __device__ __forceinline__ void wave_fft_lds(cx<T>* buf, const cx<T>* __restrict__ tw, int j, bool act) {
   constexpr int LPS = N / 9;
   cx<T> v[9];
-  __builtin_amdgcn_wave_barrier();
+  fft_sync<N>();
   if (act) {
 #pragma unroll
     for (int r = 0; r < 9; ++r) v[r] = buf[j + LPS * r];
@@ -167,7 +179,7 @@ __device__ __forceinline__ void wave_fft_lds(cx<T>* buf, const cx<T>* __restrict
 template <typename T, int N, int S>
 __device__ __forceinline__ void wave_fft_regs(cx<T> (&v)[9], cx<T>* buf, const cx<T>* __restrict__ tw, int j,
                                               bool act, cx<T> (&out)[9]) {
-  __builtin_amdgcn_wave_barrier();
+  fft_sync<N>();
   if constexpr (N == 9) {
     if (act) {
       dft<T, 9, S>(v);
@@ -180,7 +192,7 @@ __device__ __forceinline__ void wave_fft_regs(cx<T> (&v)[9], cx<T>* buf, const c
 #pragma unroll
       for (int r = 0; r < 9; ++r) buf[9 * j + r] = v[r];
     }
-    __builtin_amdgcn_wave_barrier();
+    fft_sync<N>();
     wfft_detail::stages_from<T, N, S, 9, true>(buf, tw, j, act, out);
   }
 }
@@ -191,7 +203,7 @@ __device__ __forceinline__ void wave_fft_lds_regs(cx<T>* buf, const cx<T>* __res
                                                   cx<T> (&out)[9]) {
   constexpr int LPS = N / 9;
   cx<T> v[9];
-  __builtin_amdgcn_wave_barrier();
+  fft_sync<N>();
   if (act) {
 #pragma unroll
     for (int r = 0; r < 9; ++r) v[r] = buf[j + LPS * r];
