@@ -129,6 +129,11 @@ struct Group {
   char* ws = nullptr;
   Layout lay;
   std::vector<DevState> host_states;
+  // pinned host copies of the group's device states, current and initial
+  // (nprob entries each; null: the states are copied back)
+  DevState* pinned = nullptr;
+  DevState* pinned_initial = nullptr;
+  bool initial_pending = false;  // the initial states are on their way to pinned_initial
   int warm_used = 0;
   std::vector<int> warm_flags;  // warm start taken, per problem
   bool warm_any = false;        // batched: some problem brings a warm start
@@ -207,6 +212,10 @@ struct lshom_ctx {
   std::map<std::vector<long long>, std::map<std::pair<int, int>, hipGraphExec_t>> batch_graphs;
   std::map<lshom::SchedKey, lshom::Schedule> schedules;  // autotuned or set by the caller
   lshom::PassTimer timer;
+  // pinned host memory for the states of the running solve; grows to the
+  // largest batch, freed with the context
+  lshom::DevState* pinned = nullptr;
+  size_t pinned_states = 0;
   // streams of the grid groups of a batched solve (one host thread each)
   std::vector<hipStream_t> group_streams;
   std::mutex err_mutex;  // fail() from those threads

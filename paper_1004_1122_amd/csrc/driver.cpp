@@ -6,7 +6,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
-
+#include <memory>
 #include <mutex>
 
 #include "ctx.hpp"
@@ -806,11 +806,36 @@ hipError_t enq_mix_refresh(Group& g, const Bufs<double>& b64, const Bufs<float>&
   return enq_finalize(g, FZ_REFRESH, col0_block_count(g, b64), gate);
 }
 
+// The device states on their way to the host (part of a captured block), and
+// the wait for them.
+hipError_t enq_states(Group& g) {
+  if (!g.pinned) return hipSuccess;
+  return launch_state_export(dev_state(g), g.pinned, g.nprob, stream_of(g));
+}
+
+hipError_t wait_states(Group& g) {
+  hipError_t e = hipSuccess;
+  if (!g.pinned)
+    e = hipMemcpyAsync(g.host_states.data(), dev_state(g), sizeof(DevState) * g.nprob, hipMemcpyDeviceToHost,
+                       stream_of(g));
+  if (e == hipSuccess) e = hipStreamSynchronize(stream_of(g));
+  if (e == hipSuccess && g.pinned) std::memcpy(g.host_states.data(), g.pinned, sizeof(DevState) * g.nprob);
+  return e;
+}
+
 hipError_t sync_states(Group& g) {
-  hipError_t e = hipMemcpyAsync(g.host_states.data(), dev_state(g), sizeof(DevState) * g.nprob,
-                                hipMemcpyDeviceToHost, stream_of(g));
-  if (e != hipSuccess) return e;
-  return hipStreamSynchronize(stream_of(g));
+  const hipError_t e = enq_states(g);
+  return e != hipSuccess ? e : wait_states(g);
+}
+
+// Initial scalars of every problem: as an argument for a single problem, else
+// staged through the (then unused) partials area.
+hipError_t enq_initial_states(Group& g, const std::vector<DevState>& init) {
+  if (g.nprob == 1) return launch_state_init(dev_state(g), init[0], stream_of(g));
+  DevState* staged = reinterpret_cast<DevState*>(g.ws + g.lay.off_partials);
+  const hipError_t e = hipMemcpyAsync(staged, init.data(), sizeof(DevState) * g.nprob, hipMemcpyHostToDevice,
+                                      stream_of(g));
+  return e != hipSuccess ? e : launch_state_copy(dev_state(g), staged, g.nprob, stream_of(g));
 }
 
 bool all_done(const Group& g) {
@@ -833,7 +858,10 @@ int ladder_rows(int nprob, int n_live) {
   }
 }
 
-// Run blocks of work until the device reports every problem done.  A block is
+// Run blocks of work until the device reports every problem done.  host_states
+// hold the states at the start, or zeros with initial_pending set: the first
+// block then runs without waiting for the initial ones (a problem already done
+// skips it), which are read when it has ended.  A block is
 // captured once into a HIP graph and replayed (cached per key when the group
 // has a cache); with K == 0 it is queued eagerly.  In a batch, the launches
 // cover only the unfinished problems once enough have finished: a block then
@@ -869,7 +897,6 @@ int next_block_length(const Group& g, int per, const std::vector<double>& rr_pre
 template <typename F>
 lshom_status run_blocks(Group& g, int key, int K, int per, bool adapt, F&& enqueue_block) {
   lshom_ctx* c = g.ctx;
-  HIP_TRY(c, sync_states(g));
   // the tail of a batch (few unfinished problems) may run with its own
   // schedules; the group's own ones come back on every exit
   const Schedule main_sched[2] = {current_schedule(g, LSHOM_PRECISION_FP64),
@@ -895,7 +922,8 @@ lshom_status run_blocks(Group& g, int key, int K, int per, bool adapt, F&& enque
       hipError_t e = launch_compact_live(dev_state(g), g.nprob, g.live_rows, live_dev, stream_of(g));
       if (e != hipSuccess) return e;
     }
-    return enqueue_block(n);
+    const hipError_t e = enqueue_block(n);
+    return e != hipSuccess ? e : enq_states(g);
   };
   // graphs per (rows, block length): the group's cache, else owned here
   std::map<std::pair<int, int>, hipGraphExec_t> owned;
@@ -968,7 +996,7 @@ lshom_status run_blocks(Group& g, int key, int K, int per, bool adapt, F&& enque
       it_prev[p] = g.host_states[p].iter_a;
     }
     hipError_t e = ex ? hipGraphLaunch(ex, stream_of(g)) : enqueue(n);
-    if (e == hipSuccess) e = sync_states(g);
+    if (e == hipSuccess) e = wait_states(g);
     long long after = 0, moves_after = 0;
     if (e == hipSuccess) {
       for (const DevState& s : g.host_states) {
@@ -976,6 +1004,9 @@ lshom_status run_blocks(Group& g, int key, int K, int per, bool adapt, F&& enque
         moves_after += s.iter_a + s.n_refresh;
       }
       e = harvest_timing(g, after - before);
+      if (g.initial_pending)
+        for (int p = 0; p < g.nprob; ++p) rr_prev[p] = g.pinned_initial[p].rr_log;
+      g.initial_pending = false;
     }
     if (e != hipSuccess) {
       st = fail(c, LSHOM_ERR_HIP, std::string("iteration block: ") + hipGetErrorString(e));
@@ -995,6 +1026,33 @@ lshom_status run_blocks(Group& g, int key, int K, int per, bool adapt, F&& enque
 // Workspace preparation
 // ---------------------------------------------------------------------------
 
+namespace {
+
+// Twiddle tables of one axis length in both precisions, formed once per
+// process and length (long double sines: about 0.1 ms for 729 points, paid by
+// every batched call before); the table of lengths stays small.
+struct TwiddleTables {
+  std::vector<double> t64;
+  std::vector<float> t32;
+};
+
+std::shared_ptr<const TwiddleTables> twiddle_tables(int n) {
+  static std::mutex m;
+  static std::map<int, std::shared_ptr<const TwiddleTables>> cache;
+  std::lock_guard<std::mutex> lock(m);
+  auto it = cache.find(n);
+  if (it != cache.end()) return it->second;
+  auto t = std::make_shared<TwiddleTables>();
+  twiddles(n, &t->t64);
+  t->t32.resize(t->t64.size());
+  for (size_t i = 0; i < t->t64.size(); ++i) t->t32[i] = (float)t->t64[i];
+  if (cache.size() >= 64) cache.clear();
+  cache.emplace(n, t);
+  return t;
+}
+
+}  // namespace
+
 lshom_status prepare_workspace(Group& g, const std::vector<double>& cond, const std::vector<ProbEntry>* tab,
                                const std::vector<const uint8_t*>& phases) {
   lshom_ctx* c = g.ctx;
@@ -1007,40 +1065,35 @@ lshom_status prepare_workspace(Group& g, const std::vector<double>& cond, const 
     hipStream_t s;
     ~SyncOnExit() { (void)hipStreamSynchronize(s); }
   };
-  std::vector<std::vector<double>> tw64(g.d);
-  std::vector<std::vector<float>> tw32(g.d);
   const int np = g.nprob;
-  std::vector<DevState> zero(np);
-  std::vector<double> c64((size_t)kCondStride * np, 0.0);
-  std::vector<float> c32((size_t)kCondStride * np, 0.0f);
+  // two uploads: states (zero) and problem table; conductivities and twiddles
+  // (each pair of arrays and what lies between is consecutive in the layout)
+  std::vector<char> head(use.off_partials - use.off_state, 0);
+  std::vector<char> tables(use.off_v64[0] - use.off_cond64, 0);
+  if (tab) std::memcpy(head.data() + (use.off_tab - use.off_state), tab->data(), tab->size() * sizeof(ProbEntry));
+  double* c64 = reinterpret_cast<double*>(tables.data());
+  float* c32 = reinterpret_cast<float*>(tables.data() + (use.off_cond32 - use.off_cond64));
   for (int p = 0; p < np; ++p)
     for (int i = 0; i < g.n_phases; ++i) {
       c64[(size_t)p * kCondStride + i] = cond[(size_t)p * g.n_phases + i];
       c32[(size_t)p * kCondStride + i] = (float)cond[(size_t)p * g.n_phases + i];
     }
-  HIP_TRY(c, hipMemcpyAsync(g.ws + use.off_cond64, c64.data(), c64.size() * sizeof(double), hipMemcpyHostToDevice, stream_of(g)));
-  HIP_TRY(c, hipMemcpyAsync(g.ws + use.off_cond32, c32.data(), c32.size() * sizeof(float), hipMemcpyHostToDevice, stream_of(g)));
   for (int a = 0; a < g.d; ++a) {
-    twiddles((int)g.N[a], &tw64[a]);
-    tw32[a].resize(tw64[a].size());
-    for (size_t i = 0; i < tw64[a].size(); ++i) tw32[a][i] = (float)tw64[a][i];
-    HIP_TRY(c, hipMemcpyAsync(g.ws + use.off_tw64[a], tw64[a].data(), tw64[a].size() * sizeof(double),
-                              hipMemcpyHostToDevice, stream_of(g)));
-    HIP_TRY(c, hipMemcpyAsync(g.ws + use.off_tw32[a], tw32[a].data(), tw32[a].size() * sizeof(float),
-                              hipMemcpyHostToDevice, stream_of(g)));
+    const std::shared_ptr<const TwiddleTables> t = twiddle_tables((int)g.N[a]);
+    std::memcpy(tables.data() + (use.off_tw64[a] - use.off_cond64), t->t64.data(), t->t64.size() * sizeof(double));
+    std::memcpy(tables.data() + (use.off_tw32[a] - use.off_cond64), t->t32.data(), t->t32.size() * sizeof(float));
   }
-  if (tab)
-    HIP_TRY(c, hipMemcpyAsync(g.ws + use.off_tab, tab->data(), tab->size() * sizeof(ProbEntry), hipMemcpyHostToDevice, stream_of(g)));
   SyncOnExit sync_guard{stream_of(g)};
-  HIP_TRY(c, hipMemcpyAsync(g.ws + use.off_state, zero.data(), sizeof(DevState) * np, hipMemcpyHostToDevice,
-                            stream_of(g)));
+  HIP_TRY(c, hipMemcpyAsync(g.ws + use.off_state, head.data(), head.size(), hipMemcpyHostToDevice, stream_of(g)));
+  HIP_TRY(c, hipMemcpyAsync(g.ws + use.off_cond64, tables.data(), tables.size(), hipMemcpyHostToDevice, stream_of(g)));
   g.host_states.assign(np, DevState{});
   // every phase index must name a conductivity: one maximum per image into
-  // the (still unused) partial-sum area, read back with one synchronisation
+  // the (still unused) partial-sum area, one launch, one synchronisation
   unsigned* mx = reinterpret_cast<unsigned*>(g.ws + use.off_partials);
   const size_t nimg = phases.size();
   HIP_TRY(c, hipMemsetAsync(mx, 0, sizeof(unsigned) * nimg, stream_of(g)));
-  for (size_t i = 0; i < nimg; ++i) HIP_TRY(c, launch_max_phase(phases[i], g.nvox, mx + i, stream_of(g)));
+  HIP_TRY(c, launch_max_phase(tab ? reinterpret_cast<const ProbEntry*>(g.ws + use.off_tab) : nullptr, phases[0],
+                              (int)nimg, g.nvox, mx, stream_of(g)));
   std::vector<unsigned> host_max(nimg, 0u);
   HIP_TRY(c, hipMemcpyAsync(host_max.data(), mx, sizeof(unsigned) * nimg, hipMemcpyDeviceToHost, stream_of(g)));
   HIP_TRY(c, hipStreamSynchronize(stream_of(g)));
@@ -1085,19 +1138,13 @@ lshom_status solve_group(Group& g, const std::vector<DevState>& init, const lsho
   const double* E = nullptr;
   cx<double>* x64 = b64.v[0];
   cx<double>* r64 = b64.v[1];
-  DevState* init_dev = reinterpret_cast<DevState*>(g.ws + g.lay.off_partials);  // staged, then reused
-  // initial scalars: staged through the partials area (overwritten later)
-  HIP_TRY(c, hipMemcpyAsync(init_dev, init.data(), sizeof(DevState) * g.nprob, hipMemcpyHostToDevice,
-                            stream_of(g)));
-  HIP_TRY(c, launch_state_copy(dev_state(g), init_dev, g.nprob, stream_of(g)));
-  HIP_TRY(c, launch_fill_zero(x64, nall, stream_of(g)));
   Bufs<float> b32{};
   if (mixed) {
     b32 = get_bufs<float>(g);
-    HIP_TRY(c, launch_fill_zero(b32.v[0], nall, stream_of(g)));
-    HIP_TRY(c, launch_fill_zero(b32.v[2], nall, stream_of(g)));
+    HIP_TRY(c, launch_fill_zero(x64, nall, stream_of(g)));
+    HIP_TRY(c, launch_fill_zero2(b32.v[0], b32.v[2], nall, stream_of(g)));
   } else {
-    HIP_TRY(c, launch_fill_zero(b64.v[2], nall, stream_of(g)));
+    HIP_TRY(c, launch_fill_zero2(x64, b64.v[2], nall, stream_of(g)));
   }
   const int fin_init = mixed ? FZ_REFRESH_INIT : FZ_CHECK;
   const int init_region = mixed ? PART_AUX : PART_RR0;
@@ -1107,6 +1154,7 @@ lshom_status solve_group(Group& g, const std::vector<DevState>& init, const lsho
   // pass reads a missing one as zero)
   const bool warm_batch = g.batched && g.warm_any;
   if (x0 || warm_batch) {
+    HIP_TRY(c, enq_initial_states(g, init));
     // residual of E for the admissibility test, then of E + P x0
     HIP_TRY(c, (enq_residual_of_E<double>(g, b64, E, r64, PART_AUX)));
     HIP_TRY(c, enq_finalize(g, FZ_AUX, ncol, GATE_ALWAYS));
@@ -1134,19 +1182,13 @@ lshom_status solve_group(Group& g, const std::vector<DevState>& init, const lsho
       // some problems of the batch start from e = E: every residual is
       // formed again from the (partly zeroed) iterates with the initial
       // scalars (the kept warm starts get the same values as before)
-      HIP_TRY(c, hipMemcpyAsync(init_dev, init.data(), sizeof(DevState) * g.nprob, hipMemcpyHostToDevice,
-                                stream_of(g)));
-      HIP_TRY(c, launch_state_copy(dev_state(g), init_dev, g.nprob, stream_of(g)));
+      HIP_TRY(c, enq_initial_states(g, init));
       HIP_TRY(c, (enq_true_residual<double>(g, b64, x64, E, r64, init_region, GATE_ALWAYS, eq_loop)));
       HIP_TRY(c, enq_finalize(g, fin_init, mixed ? ncol : 0, GATE_ALWAYS, eq_loop));
     }
   }
   if (!warm_used) {
-    // the staged initial states were consumed above only in the warm path;
-    // reload them (the partials area is overwritten by the residual)
-    HIP_TRY(c, hipMemcpyAsync(init_dev, init.data(), sizeof(DevState) * g.nprob, hipMemcpyHostToDevice,
-                              stream_of(g)));
-    HIP_TRY(c, launch_state_copy(dev_state(g), init_dev, g.nprob, stream_of(g)));
+    HIP_TRY(c, enq_initial_states(g, init));
     // the basic scheme tests each iterate inside its own step
     if (!ffth) {
       HIP_TRY(c, (enq_residual_of_E<double>(g, b64, E, r64, init_region, eq_loop)));
@@ -1154,7 +1196,13 @@ lshom_status solve_group(Group& g, const std::vector<DevState>& init, const lsho
     }
   }
   if (mixed) HIP_TRY(c, launch_mix_convert(mix_args(g, b64, b32, GATE_ALWAYS), stream_of(g)));
-  // (run_blocks starts by reading the states back)
+  // the first block does not wait for the initial scalars (the basic scheme
+  // has none: its first step forms them)
+  g.initial_pending = g.pinned_initial != nullptr && !ffth;
+  if (g.initial_pending)
+    HIP_TRY(c, launch_state_export(dev_state(g), g.pinned_initial, g.nprob, stream_of(g)));
+  if (g.initial_pending || ffth) g.host_states.assign(g.nprob, DevState{});
+  else HIP_TRY(c, sync_states(g));
   int max_iter = 0;
   for (const DevState& s : init) max_iter = std::max(max_iter, s.max_iter);
   // with pass timing on, the blocks are queued eagerly (events around each launch)

@@ -497,11 +497,17 @@ long long bicg_blocks(const BicgArgs& a);
 hipError_t launch_state_init(DevState* st, const DevState& init, hipStream_t s);
 // copy nprob initial states from device memory src into st
 hipError_t launch_state_copy(DevState* st, const DevState* src, int nprob, hipStream_t s);
+// nprob states into pinned host memory (valid after the stream is synchronised)
+hipError_t launch_state_export(const DevState* st, DevState* host, int nprob, hipStream_t s);
 // live[0..rows): the problems whose state is not done, in index order, then
 // done problems to fill the rows (the host picks rows >= the count not done).
 hipError_t launch_compact_live(const DevState* st, int nprob, int rows, int* live, hipStream_t s);
 template <typename T> hipError_t launch_fill_zero(cx<T>* p, long long n, hipStream_t s);
-hipError_t launch_max_phase(const uint8_t* ph, long long n, unsigned* out, hipStream_t s);
+template <typename T> hipError_t launch_fill_zero2(cx<T>* p, cx<T>* q, long long n, hipStream_t s);
+// out[i] (zero on entry): the largest phase index of image i (n nodes); the
+// images of a problem table, or (tab null) the one image ph
+hipError_t launch_max_phase(const ProbEntry* tab, const uint8_t* ph, int images, long long n, unsigned* out,
+                            hipStream_t s);
 // counts[0..256): nodes of each phase index (counts zero on entry)
 hipError_t launch_phase_histogram(const uint8_t* ph, long long n, unsigned* counts, hipStream_t s);
 

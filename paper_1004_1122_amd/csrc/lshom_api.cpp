@@ -115,6 +115,28 @@ void fill_info(const DevState& hs, double l0, const lshom_solve_opts& o, int war
   }
 }
 
+// Pinned host memory for the states of `states` problems, twice (the states
+// after a block and the initial ones; grown, never shrunk; none if the allocation fails: the states are then copied back).
+// Captured launches hold its address.
+void ensure_pinned(lshom_ctx* c, size_t states) {
+  if (c->pinned_states >= states) return;
+  (void)hipStreamSynchronize(c->stream);
+  drop_graphs(c->graphs);
+  drop_batch_graphs(c);
+  if (c->pinned) (void)hipHostFree(c->pinned);
+  c->pinned = nullptr;
+  c->pinned_states = 0;
+  void* p = nullptr;
+  if (hipHostMalloc(&p, 2 * states * sizeof(DevState), hipHostMallocDefault) == hipSuccess) {
+    c->pinned = static_cast<DevState*>(p);
+    c->pinned_states = states;
+  } else {
+    (void)hipGetLastError();
+  }
+  c->g.pinned = c->pinned;
+  c->g.pinned_initial = c->pinned ? c->pinned + c->pinned_states : nullptr;
+}
+
 hipError_t order_after_user(lshom_ctx* c) {
   std::lock_guard<std::mutex> lock(setup_mutex());
   hipError_t e = hipEventRecord(c->ev, c->user_stream);
@@ -284,6 +306,7 @@ lshom_status lshom_create(lshom_ctx** out, int device, void* hip_stream) {
     delete c;
     return LSHOM_ERR_HIP;
   }
+  ensure_pinned(c, 64);
   *out = c;
   return LSHOM_OK;
 }
@@ -296,6 +319,7 @@ void lshom_destroy(lshom_ctx* c) {
   drop_batch_graphs(c);
   for (hipEvent_t ev : c->timer.pool) (void)hipEventDestroy(ev);
   if (c->ev) (void)hipEventDestroy(c->ev);
+  if (c->pinned) (void)hipHostFree(c->pinned);
   for (hipStream_t st : c->group_streams) (void)hipStreamDestroy(st);
   if (c->stream) (void)hipStreamDestroy(c->stream);
   delete c;
@@ -317,6 +341,8 @@ lshom_status lshom_set_microstructure(lshom_ctx* c, int d, const int64_t* N,
   c->g = Group{};
   c->g.ctx = c;
   c->g.graph_cache = &c->graphs;
+  c->g.pinned = c->pinned;
+  c->g.pinned_initial = c->pinned ? c->pinned + c->pinned_states : nullptr;
   if (group_setup(c->g, d, N, n_phases) != LSHOM_OK)
     return fail(c, LSHOM_ERR_UNSUPPORTED, "grid too long for one LDS-resident FFT batch");
   c->g.phase = phase_dev;
@@ -378,6 +404,8 @@ lshom_status lshom_set_microstructure_tensor(lshom_ctx* c, int d, const int64_t*
   c->g = Group{};
   c->g.ctx = c;
   c->g.graph_cache = &c->graphs;
+  c->g.pinned = c->pinned;
+  c->g.pinned_initial = c->pinned ? c->pinned + c->pinned_states : nullptr;
   if (group_setup(c->g, d, N, n_phases, true) != LSHOM_OK)
     return fail(c, LSHOM_ERR_UNSUPPORTED, "grid too long for one LDS-resident FFT batch");
   c->g.phase = phase_dev;
@@ -980,14 +1008,20 @@ lshom_status lshom_solve_batched(lshom_ctx* c, int32_t n, const lshom_problem* p
   std::vector<std::vector<ProbEntry>> tabs(ng);
   std::vector<std::vector<DevState>> inits(ng);
   if (c->batch_graphs.size() + ng > 64) drop_batch_graphs(c);
+  ensure_pinned(c, (size_t)n);
+  size_t pinned_at = 0;
   for (size_t gi = 0; gi < ng; ++gi) {
     Group& g = bp.groups[gi];
+    g.pinned = c->pinned ? c->pinned + pinned_at : nullptr;
+    g.pinned_initial = c->pinned ? g.pinned + c->pinned_states : nullptr;
+    pinned_at += (size_t)g.nprob;
     if ((s = prepare_batch_group(c, bp, gi, probs, ws_dev, o, &tabs[gi], &inits[gi])) != LSHOM_OK) return s;
     // the captured launches carry the group's wave-vector scale 1 / Y (cell
     // side lengths) as kernel arguments, so the cell is part of the tag
     std::vector<long long> tag = {(long long)reinterpret_cast<uintptr_t>(g.ws), g.d, (long long)g.N[0],
                                   (long long)g.N[1], (long long)g.N[2], g.nprob, g.n_phases,
-                                  (long long)g.lay.total, g.lay.has32 ? 1 : 0};
+                                  (long long)g.lay.total, g.lay.has32 ? 1 : 0,
+                                  (long long)reinterpret_cast<uintptr_t>(g.pinned)};
     for (int a = 0; a < 3; ++a) {
       long long bits;
       std::memcpy(&bits, &g.cell_inv[a], sizeof(bits));

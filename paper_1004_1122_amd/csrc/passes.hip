@@ -1365,8 +1365,18 @@ __global__ __launch_bounds__(256) void state_copy_kernel(DevState* st, const Dev
   if (i < nprob) st[i] = src[i];
 }
 
+// Eight bytes a thread, straight to the host's pinned copy: a read-back of the
+// states costs one small launch and the wait, no copy engine (a hipMemcpy of
+// a few hundred bytes to pageable memory put about 20 us in every block of
+// iterations).
+__global__ __launch_bounds__(256) void state_export_kernel(const DevState* st, DevState* host, int words) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i < words) reinterpret_cast<long long*>(host)[i] = reinterpret_cast<const long long*>(st)[i];
+}
+
 template <typename T>
-__global__ __launch_bounds__(256) void fill_zero_kernel(cx<T>* p, long long n) {
+__global__ __launch_bounds__(256) void fill_zero_kernel(cx<T>* p, cx<T>* q, long long n) {
+  if (blockIdx.y == 1) p = q;
   const long long stride = (long long)gridDim.x * 256;
   for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < n; i += stride)
     p[i] = cx<T>{T(0), T(0)};
@@ -1448,18 +1458,47 @@ static int pick_threads(int points, const FftPlan& plan, size_t lds) {
   return heavy > 128 && 5 * lds > 160 * 1024 ? 256 : 128;
 }
 
-// Largest phase index of a phase image (validation at workspace set-up).
-__global__ __launch_bounds__(256) void max_phase_kernel(const uint8_t* ph, long long n, unsigned* out) {
+// Largest phase index of each image (validation at workspace set-up): 16
+// bytes a load where the image is aligned, one atomic per block.  One launch
+// for all images of a batch: a launch each took 12 us and more per image.
+__global__ __launch_bounds__(256) void max_phase_kernel(const ProbEntry* tab, const uint8_t* one, long long n,
+                                                        unsigned* out) {
+  __shared__ unsigned red[4];
+  const uint8_t* ph = tab ? tab[blockIdx.y].phase : one;
+  const long long stride = (long long)gridDim.x * 256, t0 = (long long)blockIdx.x * 256 + threadIdx.x;
   unsigned m = 0;
-  const long long stride = (long long)gridDim.x * 256;
-  for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < n; i += stride) m = max(m, (unsigned)ph[i]);
+  const bool wide = (reinterpret_cast<uintptr_t>(ph) & 15u) == 0;
+  const long long nw = wide ? n / 16 : 0;
+  auto word = [&](uint32_t w) {
+    m = max(m, max(max(w & 255u, (w >> 8) & 255u), max((w >> 16) & 255u, w >> 24)));
+  };
+  const uint4* p16 = reinterpret_cast<const uint4*>(ph);
+  for (long long i = t0; i < nw; i += stride) {
+    const uint4 v = p16[i];
+    word(v.x);
+    word(v.y);
+    word(v.z);
+    word(v.w);
+  }
+  for (long long i = 16 * nw + t0; i < n; i += stride) m = max(m, (unsigned)ph[i]);
   for (int off = 32; off > 0; off >>= 1) m = max(m, (unsigned)__shfl_down((int)m, off, 64));
-  if ((threadIdx.x & 63) == 0) atomicMax(out, m);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
+  __syncthreads();
+  if (threadIdx.x == 0) atomicMax(out + blockIdx.y, max(max(red[0], red[1]), max(red[2], red[3])));
 }
 
-hipError_t launch_max_phase(const uint8_t* ph, long long n, unsigned* out, hipStream_t s) {
-  hipLaunchKernelGGL(max_phase_kernel, dim3((unsigned)update_blocks(n)), dim3(256), 0, s, ph, n, out);
-  return hipGetLastError();
+hipError_t launch_max_phase(const ProbEntry* tab, const uint8_t* ph, int images, long long n, unsigned* out,
+                            hipStream_t s) {
+  const long long blocks = std::max<long long>(1, std::min<long long>((n + 16383) / 16384, 1024));
+  // grid rows are limited to 65535
+  for (int i0 = 0; i0 < images; i0 += 32768) {
+    const int rows = std::min(images - i0, 32768);
+    hipLaunchKernelGGL(max_phase_kernel, dim3((unsigned)blocks, (unsigned)rows), dim3(256), 0, s,
+                       tab ? tab + i0 : nullptr, ph, n, out + i0);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 // Node count of every phase index (256 bins): block counts in LDS, then one
@@ -1647,9 +1686,22 @@ hipError_t launch_state_init(DevState* st, const DevState& init, hipStream_t s) 
   return hipGetLastError();
 }
 
+hipError_t launch_state_export(const DevState* st, DevState* host, int nprob, hipStream_t s) {
+  static_assert(sizeof(DevState) % sizeof(long long) == 0, "exported in 8-byte words");
+  const int words = nprob * (int)(sizeof(DevState) / sizeof(long long));
+  hipLaunchKernelGGL(state_export_kernel, dim3((unsigned)((words + 255) / 256)), dim3(256), 0, s, st, host, words);
+  return hipGetLastError();
+}
+
 template <typename T>
 hipError_t launch_fill_zero(cx<T>* p, long long n, hipStream_t s) {
-  hipLaunchKernelGGL(fill_zero_kernel<T>, dim3((unsigned)update_blocks(n)), dim3(256), 0, s, p, n);
+  hipLaunchKernelGGL(fill_zero_kernel<T>, dim3((unsigned)update_blocks(n)), dim3(256), 0, s, p, p, n);
+  return hipGetLastError();
+}
+
+template <typename T>
+hipError_t launch_fill_zero2(cx<T>* p, cx<T>* q, long long n, hipStream_t s) {
+  hipLaunchKernelGGL(fill_zero_kernel<T>, dim3((unsigned)update_blocks(n), 2), dim3(256), 0, s, p, q, n);
   return hipGetLastError();
 }
 
@@ -1663,6 +1715,8 @@ template hipError_t launch_flush_x<double>(const UpdArgs<double>&, hipStream_t);
 template hipError_t launch_flush_x<float>(const UpdArgs<float>&, hipStream_t);
 template hipError_t launch_fill_zero<double>(cx<double>*, long long, hipStream_t);
 template hipError_t launch_fill_zero<float>(cx<float>*, long long, hipStream_t);
+template hipError_t launch_fill_zero2<double>(cx<double>*, cx<double>*, long long, hipStream_t);
+template hipError_t launch_fill_zero2<float>(cx<float>*, cx<float>*, long long, hipStream_t);
 template long long row_blocks<double>(const RowArgs<double>&);
 template long long row_blocks<float>(const RowArgs<float>&);
 template long long col_blocks<double>(const ColArgs<double>&);
