@@ -859,9 +859,9 @@ int ladder_rows(int nprob, int n_live) {
 }
 
 // Run blocks of work until the device reports every problem done.  host_states
-// hold the states at the start, or zeros with initial_pending set: the first
-// block then runs without waiting for the initial ones (a problem already done
-// skips it), which are read when it has ended.  A block is
+// hold the states at the start, or zeros with initial_pending set: they are then
+// read while enqueue_first's iterations run (without it, when the first block
+// has ended: a problem already done skips it).  A block is
 // captured once into a HIP graph and replayed (cached per key when the group
 // has a cache); with K == 0 it is queued eagerly.  In a batch, the launches
 // cover only the unfinished problems once enough have finished: a block then
@@ -894,8 +894,15 @@ int next_block_length(const Group& g, int per, const std::vector<double>& rr_pre
   return n;
 }
 
-template <typename F>
-lshom_status run_blocks(Group& g, int key, int K, int per, bool adapt, F&& enqueue_block) {
+// Iterations queued before the host looks at the initial states: they cover
+// the time it needs to read them and to launch the first block (some 25 us; an
+// iteration takes 20 us or more).  A solve whose start is converged then skips
+// that block, whose 16 gated-out iterations took 70 to 110 us in 2-D.
+constexpr int kFirstIterations = 2;
+
+lshom_status run_blocks(Group& g, int key, int K, int per, bool adapt,
+                        const std::function<hipError_t(int)>& enqueue_block,
+                        const std::function<hipError_t()>& enqueue_first = nullptr) {
   lshom_ctx* c = g.ctx;
   // the tail of a batch (few unfinished problems) may run with its own
   // schedules; the group's own ones come back on every exit
@@ -965,6 +972,22 @@ lshom_status run_blocks(Group& g, int key, int K, int per, bool adapt, F&& enque
   lshom_status st = LSHOM_OK;
   std::vector<double> rr_prev(g.nprob, -1.0);
   std::vector<int> it_prev(g.nprob, 0);
+  if (g.initial_pending && enqueue_first) {
+    // the host reads the initial states while the first iterations run
+    struct Event {
+      hipEvent_t ev = nullptr;
+      ~Event() {
+        if (ev) (void)hipEventDestroy(ev);
+      }
+    } here;
+    hipError_t e = hipEventCreateWithFlags(&here.ev, hipEventDisableTiming);
+    if (e == hipSuccess) e = hipEventRecord(here.ev, stream_of(g));
+    if (e == hipSuccess) e = enqueue_first();
+    if (e == hipSuccess) e = hipEventSynchronize(here.ev);
+    g.initial_pending = false;
+    if (e != hipSuccess) return fail(c, LSHOM_ERR_HIP, std::string("first iterations: ") + hipGetErrorString(e));
+    std::memcpy(g.host_states.data(), g.pinned_initial, sizeof(DevState) * g.nprob);
+  }
   // the device sets `done` at the latest after max_iter iterations; every
   // block advances an iteration or (mixed precision) a refresh of some live
   // problem, so a block that advances neither means the state stopped
@@ -1219,6 +1242,14 @@ lshom_status solve_group(Group& g, const std::vector<DevState>& init, const lsho
   lshom_status s;
   // the blocks take the buffers (and launch shapes) current when they are
   // queued: the tail of a batch may switch schedules
+  const auto first_iterations = [&]() -> hipError_t {
+    for (int k = 0; k < kFirstIterations; ++k) {
+      const hipError_t e = mixed ? enq_cg_iteration<float>(g, get_bufs<float>(g), GATE_NO_REFRESH)
+                                 : enq_cg_iteration<double>(g, get_bufs<double>(g), GATE_ACTIVE);
+      if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+  };
   if (ffth) {
     s = run_blocks(g, 3 + eq_loop, K, per, adapt, [&](int n) -> hipError_t {
       const Bufs<double> f64 = get_bufs<double>(g);
@@ -1236,7 +1267,7 @@ lshom_status solve_group(Group& g, const std::vector<DevState>& init, const lsho
         if (e != hipSuccess) return e;
       }
       return enq_finalize(g, FZ_CHECK, 0, GATE_ACTIVE, eq_loop);
-    });
+    }, first_iterations);
   } else {
     // a refresh may cut a block short: at least one iteration per block is certain
     s = run_blocks(g, 1, K, per, adapt, [&](int n) -> hipError_t {
@@ -1247,7 +1278,7 @@ lshom_status solve_group(Group& g, const std::vector<DevState>& init, const lsho
         if (e != hipSuccess) return e;
       }
       return enq_mix_refresh(g, f64, f32, E, GATE_REFRESH);
-    });
+    }, first_iterations);
   }
   if (s != LSHOM_OK) return s;
   if (!ffth) {
