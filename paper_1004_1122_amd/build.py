@@ -24,6 +24,7 @@ SOURCES = [
     "passes.hip",
     "wave3d.hip",
     "wave2d.hip",
+    "resident2d.hip",
     "plan.cpp",
     "driver.cpp",
     "lshom_api.cpp",

@@ -671,6 +671,46 @@ hipError_t enq_cg_iteration(Group& g, const Bufs<T>& b, int gate) {
   return e;
 }
 
+// The iteration loop of a solve runs in one block per problem (resident2d.hip).
+bool use_resident(const Group& g, int precision) {
+  return g.d == 2 && !g.eq && !g.tensor && !g.aniso && !g.timer &&
+         resident_fits(g.N, precision == LSHOM_PRECISION_FP64 ? (int)sizeof(cx<double>) : (int)sizeof(cx<float>),
+                       lds_limit_of(g));
+}
+
+template <typename T>
+hipError_t enq_resident(Group& g, const Bufs<T>& b, int iters, bool basic, int gate) {
+  ResidentArgs<T> a{};
+  a.N0 = (int)g.N[0];
+  a.N1 = (int)g.N[1];
+  a.h = g.h;
+  a.iters = iters;
+  for (int t = 0; t < 2; ++t) {
+    a.plan[t] = b.plan[t];
+    a.tw[t] = b.tw[t];
+    a.cinv[t] = g.cell_inv[t];
+  }
+  a.phase = g.phase;
+  a.cond = b.cond;
+  a.n_phases = g.n_phases;
+  a.l0 = g.l0;
+  a.inv_n = (T)(1.0 / (double)g.nvox);
+  a.inv_nd = 1.0 / (double)g.nvox;
+  a.x = b.v[0];
+  a.r = b.v[1];
+  a.p = b.v[2];
+  a.st = dev_state(g);
+  a.parts = dev_parts(g);
+  a.gate = gate;
+  a.bt = batch_of(g);
+  a.fd_n0 = make_fastdiv((uint32_t)a.N0);
+  a.fd_n1 = make_fastdiv((uint32_t)a.N1);
+  a.fd_h = make_fastdiv((uint32_t)a.h);
+  a.ss0 = lds_odd_stride(a.N0);
+  a.ss1 = lds_odd_stride(a.N1);
+  return launch_resident(a, basic, stream_of(g));
+}
+
 // The x step of the last update, for the problems of a CG loop that stopped
 // after an update (wave passes defer it to the next direction step).
 template <typename T>
@@ -894,6 +934,9 @@ int next_block_length(const Group& g, int per, const std::vector<double>& rr_pre
   return n;
 }
 
+// Iterations of a launch that holds whole solves: bounds the launch (about
+// 20 ms at 63^2), not the solve.
+constexpr int kResidentIters = 1024;
 // Iterations queued before the host looks at the initial states: they cover
 // the time it needs to read them and to launch the first block (some 25 us; an
 // iteration takes 20 us or more).  A solve whose start is converged then skips
@@ -1242,6 +1285,7 @@ lshom_status solve_group(Group& g, const std::vector<DevState>& init, const lsho
   lshom_status s;
   // the blocks take the buffers (and launch shapes) current when they are
   // queued: the tail of a batch may switch schedules
+  const bool resident = use_resident(g, o.precision);
   const auto first_iterations = [&]() -> hipError_t {
     for (int k = 0; k < kFirstIterations; ++k) {
       const hipError_t e = mixed ? enq_cg_iteration<float>(g, get_bufs<float>(g), GATE_NO_REFRESH)
@@ -1250,7 +1294,20 @@ lshom_status solve_group(Group& g, const std::vector<DevState>& init, const lsho
     }
     return hipSuccess;
   };
-  if (ffth) {
+  if (resident && !mixed) {
+    // one launch until every problem has stopped, nothing to capture
+    s = run_blocks(g, 0, 0, kResidentIters, false, [&](int n) -> hipError_t {
+      return enq_resident<double>(g, get_bufs<double>(g), n, ffth, GATE_ACTIVE);
+    });
+  } else if (resident) {
+    // the FP32 iterations to the next refresh, then the refresh
+    s = run_blocks(g, 7, K, kResidentIters, false, [&](int n) -> hipError_t {
+      const Bufs<double> f64 = get_bufs<double>(g);
+      const Bufs<float> f32 = get_bufs<float>(g);
+      hipError_t e = enq_resident<float>(g, f32, n, false, GATE_NO_REFRESH);
+      return e != hipSuccess ? e : enq_mix_refresh(g, f64, f32, E, GATE_REFRESH);
+    });
+  } else if (ffth) {
     s = run_blocks(g, 3 + eq_loop, K, per, adapt, [&](int n) -> hipError_t {
       const Bufs<double> f64 = get_bufs<double>(g);
       for (int k = 0; k < n; ++k) {

@@ -199,6 +199,13 @@ __host__ __device__ constexpr int jobs_per_thread(int R) {
   return R <= 3 ? 4 : (R <= 5 ? 3 : (R <= 9 ? 2 : 1));
 }
 
+// The same for the kernel that holds a whole image (resident2d.hip): enough for
+// kResidentPoints points.
+constexpr int kResidentThreads = 512;
+constexpr int kResidentPerThread = 9;
+constexpr int kResidentPoints = kResidentPerThread * kResidentThreads;
+__host__ __device__ constexpr int resident_jobs_per_thread(int R) { return (kResidentPerThread + R - 1) / R; }
+
 // Largest number of points (nseq * n) one batch may hold for a plan.
 __host__ __device__ inline int plan_batch_cap(const FftPlan& p, int threads) {
   int cap = 1 << 30;
@@ -227,11 +234,10 @@ __device__ __forceinline__ cx<T> twiddle(const cx<T>* __restrict__ tw, int m) {
 // Sequence s, element e lives at buf[s * ss + e].  Twiddle table tw[m] holds
 // exp(-2 pi i m / n) for 0 <= m < n (conjugated for the inverse direction,
 // S = +1).
-template <typename T, int R, int S, int NT>
+template <typename T, int R, int S, int NT, int JM>
 __device__ __forceinline__ void fft_stage(cx<T>* buf, int nseq, int ss, int n, int Ns,
                                           const cx<T>* __restrict__ tw, int tid, const FastDiv& fnr,
                                           const FastDiv& fns) {
-  constexpr int JM = jobs_per_thread(R);
   const int NR = (int)fnr.d;
   const int jobs = nseq * NR;
   const int step = NR / Ns;  // n / (Ns R)
@@ -287,37 +293,42 @@ __host__ __device__ inline bool radix_in_set(int R, int set) {
   return (R >= 2 && R <= 9) || is_wide_prime(R);
 }
 
+template <bool RESIDENT>
+__host__ __device__ constexpr int stage_jobs(int R) {
+  return RESIDENT ? resident_jobs_per_thread(R) : jobs_per_thread(R);
+}
+
 // Transform nseq sequences of length plan.n in LDS.  Callers synchronise
 // before (data written) and may read the result right after.  Every radix of
 // the plan must belong to RS.
-template <typename T, int S, int NT, int RS>
+template <typename T, int S, int NT, int RS, bool RESIDENT = false>
 __device__ __forceinline__ void fft_lds(cx<T>* buf, int nseq, int ss, const FftPlan& plan,
                         const cx<T>* __restrict__ tw, int tid) {
   int Ns = 1;
   for (int st = 0; st < plan.nstages; ++st) {
     const int R = plan.radix[st];
     if constexpr (RS == RADIX_POW3) {
-      if (R == 9) fft_stage<T, 9, S, NT>(buf, nseq, ss, plan.n, Ns, tw, tid, plan.nr[st], plan.ns[st]);
-      else fft_stage<T, 3, S, NT>(buf, nseq, ss, plan.n, Ns, tw, tid, plan.nr[st], plan.ns[st]);
+      if (R == 9) fft_stage<T, 9, S, NT, stage_jobs<RESIDENT>(9)>(buf, nseq, ss, plan.n, Ns, tw, tid, plan.nr[st], plan.ns[st]);
+      else fft_stage<T, 3, S, NT, stage_jobs<RESIDENT>(3)>(buf, nseq, ss, plan.n, Ns, tw, tid, plan.nr[st], plan.ns[st]);
     } else if constexpr (RS == RADIX_POW2) {
-      if (R == 8) fft_stage<T, 8, S, NT>(buf, nseq, ss, plan.n, Ns, tw, tid, plan.nr[st], plan.ns[st]);
-      else if (R == 4) fft_stage<T, 4, S, NT>(buf, nseq, ss, plan.n, Ns, tw, tid, plan.nr[st], plan.ns[st]);
-      else fft_stage<T, 2, S, NT>(buf, nseq, ss, plan.n, Ns, tw, tid, plan.nr[st], plan.ns[st]);
+      if (R == 8) fft_stage<T, 8, S, NT, stage_jobs<RESIDENT>(8)>(buf, nseq, ss, plan.n, Ns, tw, tid, plan.nr[st], plan.ns[st]);
+      else if (R == 4) fft_stage<T, 4, S, NT, stage_jobs<RESIDENT>(4)>(buf, nseq, ss, plan.n, Ns, tw, tid, plan.nr[st], plan.ns[st]);
+      else fft_stage<T, 2, S, NT, stage_jobs<RESIDENT>(2)>(buf, nseq, ss, plan.n, Ns, tw, tid, plan.nr[st], plan.ns[st]);
     } else {
       switch (R) {
-        case 2: fft_stage<T, 2, S, NT>(buf, nseq, ss, plan.n, Ns, tw, tid, plan.nr[st], plan.ns[st]); break;
-        case 3: fft_stage<T, 3, S, NT>(buf, nseq, ss, plan.n, Ns, tw, tid, plan.nr[st], plan.ns[st]); break;
-        case 4: fft_stage<T, 4, S, NT>(buf, nseq, ss, plan.n, Ns, tw, tid, plan.nr[st], plan.ns[st]); break;
-        case 5: fft_stage<T, 5, S, NT>(buf, nseq, ss, plan.n, Ns, tw, tid, plan.nr[st], plan.ns[st]); break;
-        case 6: fft_stage<T, 6, S, NT>(buf, nseq, ss, plan.n, Ns, tw, tid, plan.nr[st], plan.ns[st]); break;
-        case 7: fft_stage<T, 7, S, NT>(buf, nseq, ss, plan.n, Ns, tw, tid, plan.nr[st], plan.ns[st]); break;
-        case 8: fft_stage<T, 8, S, NT>(buf, nseq, ss, plan.n, Ns, tw, tid, plan.nr[st], plan.ns[st]); break;
-        case 9: fft_stage<T, 9, S, NT>(buf, nseq, ss, plan.n, Ns, tw, tid, plan.nr[st], plan.ns[st]); break;
+        case 2: fft_stage<T, 2, S, NT, stage_jobs<RESIDENT>(2)>(buf, nseq, ss, plan.n, Ns, tw, tid, plan.nr[st], plan.ns[st]); break;
+        case 3: fft_stage<T, 3, S, NT, stage_jobs<RESIDENT>(3)>(buf, nseq, ss, plan.n, Ns, tw, tid, plan.nr[st], plan.ns[st]); break;
+        case 4: fft_stage<T, 4, S, NT, stage_jobs<RESIDENT>(4)>(buf, nseq, ss, plan.n, Ns, tw, tid, plan.nr[st], plan.ns[st]); break;
+        case 5: fft_stage<T, 5, S, NT, stage_jobs<RESIDENT>(5)>(buf, nseq, ss, plan.n, Ns, tw, tid, plan.nr[st], plan.ns[st]); break;
+        case 6: fft_stage<T, 6, S, NT, stage_jobs<RESIDENT>(6)>(buf, nseq, ss, plan.n, Ns, tw, tid, plan.nr[st], plan.ns[st]); break;
+        case 7: fft_stage<T, 7, S, NT, stage_jobs<RESIDENT>(7)>(buf, nseq, ss, plan.n, Ns, tw, tid, plan.nr[st], plan.ns[st]); break;
+        case 8: fft_stage<T, 8, S, NT, stage_jobs<RESIDENT>(8)>(buf, nseq, ss, plan.n, Ns, tw, tid, plan.nr[st], plan.ns[st]); break;
+        case 9: fft_stage<T, 9, S, NT, stage_jobs<RESIDENT>(9)>(buf, nseq, ss, plan.n, Ns, tw, tid, plan.nr[st], plan.ns[st]); break;
         default:
           if constexpr (RS == RADIX_WIDE) {
-            if (R == 11) fft_stage<T, 11, S, NT>(buf, nseq, ss, plan.n, Ns, tw, tid, plan.nr[st], plan.ns[st]);
-            else if (R == 13) fft_stage<T, 13, S, NT>(buf, nseq, ss, plan.n, Ns, tw, tid, plan.nr[st], plan.ns[st]);
-            else if (R == 17) fft_stage<T, 17, S, NT>(buf, nseq, ss, plan.n, Ns, tw, tid, plan.nr[st], plan.ns[st]);
+            if (R == 11) fft_stage<T, 11, S, NT, stage_jobs<RESIDENT>(11)>(buf, nseq, ss, plan.n, Ns, tw, tid, plan.nr[st], plan.ns[st]);
+            else if (R == 13) fft_stage<T, 13, S, NT, stage_jobs<RESIDENT>(13)>(buf, nseq, ss, plan.n, Ns, tw, tid, plan.nr[st], plan.ns[st]);
+            else if (R == 17) fft_stage<T, 17, S, NT, stage_jobs<RESIDENT>(17)>(buf, nseq, ss, plan.n, Ns, tw, tid, plan.nr[st], plan.ns[st]);
           }
           break;
       }

@@ -480,6 +480,40 @@ int w2_seqs(int n);
 template <typename T> hipError_t launch_w2_row(const RowArgs<T>& a, hipStream_t s);
 template <typename T> hipError_t launch_w2_col(const ColArgs<T>& a, hipStream_t s);
 
+// ---------------------------------------------------------------------------
+// Whole iterations of a small 2-D image in one block (resident2d.hip)
+// ---------------------------------------------------------------------------
+template <typename T>
+struct ResidentArgs {
+  int N0, N1, h;
+  int iters;                     // iterations of this launch, at most
+  FftPlan plan[2];
+  const cx<T>* tw[2];
+  double cinv[2];                // 1 / cell side lengths
+  const uint8_t* phase;          // single problem (batched: the problem table)
+  const T* cond;
+  int n_phases;
+  double l0;
+  T inv_n;
+  double inv_nd;
+  cx<T>* x;
+  cx<T>* r;
+  cx<T>* p;
+  DevState* st;
+  Partials parts;
+  int gate;
+  Batch bt;
+  FastDiv fd_n0, fd_n1, fd_h;    // N0, N1, h
+  int ss0, ss1;                  // LDS strides of column and row sequences
+};
+// Grids the kernel takes (scalar phases and an isotropic reference, which the
+// caller checks), and its LDS bytes.
+bool resident_fits(const int64_t* N, int elem_bytes, size_t lds_limit);
+// CG iterations (direction test first, as the passes take them) until the
+// problem stops, asks for a refresh (mixed) or iters are done; basic: steps of
+// the basic scheme with its test.
+template <typename T> hipError_t launch_resident(const ResidentArgs<T>& a, bool basic, hipStream_t s);
+
 // Host launchers (passes.hip).
 template <typename T> hipError_t launch_row(const RowArgs<T>& a, hipStream_t s);
 template <typename T> hipError_t launch_col(const ColArgs<T>& a, hipStream_t s);

@@ -28,8 +28,8 @@ import re
 import statistics
 
 HERE = os.path.dirname(os.path.abspath(__file__))
-KERNEL_SOURCES = ("passes.hip", "wave3d.hip", "wave2d.hip", "wave_fft.hpp", "fft_engine.hpp", "reduce.hpp",
-                  "kernels.hpp", "radix_consts.hpp")
+KERNEL_SOURCES = ("passes.hip", "wave3d.hip", "wave2d.hip", "resident2d.hip", "wave_fft.hpp",
+                  "fft_engine.hpp", "reduce.hpp", "kernels.hpp", "radix_consts.hpp")
 
 
 def code_only(text):
