@@ -149,7 +149,7 @@ struct Plan {
   size_t x, enc0a, cat0, down0, enc1a, cat1, down1, enc2a, cat2, down2, bota, botb, dec2a, dec2b, dec1a, dec1b,
       dec0a, dec0b, out;
   // training
-  size_t gout, gpre, gA, gB, dcat0, dcat1, dcat2, partial, part, loss;
+  size_t gout, gpre, gpre2, gA, skip0, skip1, skip2, partial, part, loss;
   size_t partial_floats = 0;
 };
 
@@ -194,14 +194,15 @@ Plan make_plan(const lshom_cnn* c, int B, int N, int training) {
     p.gout = f32(p.P[0] * 2);
     long long gmax = 0;
     for (int l = 0; l < 4; ++l) gmax = std::max(gmax, p.P[l] * (long long)(c0 << l));
-    p.gpre = bf(gmax > p.P[0] * 8 ? gmax : p.P[0] * 8, 1);
+    gmax = std::max(gmax, p.P[0] * 8);
+    p.gpre = bf(gmax, 1);
+    p.gpre2 = bf(gmax, 1);
     long long gab = 0;
     for (int l = 0; l < 4; ++l) gab = std::max(gab, p.P[l] * (long long)(2 * c0 << l));
     p.gA = f32(gab);
-    p.gB = f32(gab);
-    p.dcat0 = f32(p.P[0] * 2 * c0);
-    p.dcat1 = f32(p.P[1] * 4 * c0);
-    p.dcat2 = f32(p.P[2] * 8 * c0);
+    p.skip0 = f32(p.P[0] * c0);
+    p.skip1 = f32(p.P[1] * 2 * c0);
+    p.skip2 = f32(p.P[2] * 4 * c0);
     size_t pf = 0;
     const int lev_of[] = {0, 0, 1, 1, 1, 2, 2, 2, 3, 3, 3, 2, 2, 2, 1, 1, 1, 0, 0, 0, 0};
     for (size_t i = 0; i < c->layers.size(); ++i) {
@@ -263,8 +264,21 @@ hipError_t conv_fwd(lshom_cnn* c, const Layer& L, View in, int B, int Hi, int Ho
   return launch_conv(a, c->stream);
 }
 
-// input gradient of layer L: gpre [Pout][np] -> out_f [Pin][cin]
-hipError_t conv_dgrad(lshom_cnn* c, const Layer& L, const bf16_t* gpre, int B, int Hout, float* out_f) {
+// Where an input gradient goes on: through the ReLU of the activation it
+// belongs to, as the bf16 operand of the layer before (ConvArgs).
+struct GradNext {
+  const bf16_t* act = nullptr;  // activation, pixel stride lda
+  int lda = 0;
+  const float* add = nullptr;   // skip gradient, pixel stride ldadd
+  int ldadd = 0;
+  int C = 0;                    // channels of gpre
+  bf16_t* gpre = nullptr;
+};
+
+// input gradient of layer L: gpre [Pout][np] -> nx (channels < nx.C) and
+// out_f [Pin][cin - nx.C]
+hipError_t conv_dgrad(lshom_cnn* c, const Layer& L, const bf16_t* gpre, int B, int Hout, float* out_f,
+                      const GradNext& nx = GradNext{}) {
   ConvArgs a{};
   a.in0 = gpre;
   a.C0 = L.np;
@@ -279,7 +293,14 @@ hipError_t conv_dgrad(lshom_cnn* c, const Layer& L, const bf16_t* gpre, int B, i
   a.bias = nullptr;
   a.relu = 0;
   a.out_f = out_f;
-  a.ldf = L.cin;
+  a.ldf = L.cin - nx.C;
+  a.mask = nx.act;
+  a.ldm = nx.lda;
+  a.add = nx.add;
+  a.lda = nx.ldadd;
+  a.n_b = nx.C;
+  a.out_b = nx.gpre;
+  a.ldb = nx.C;
   if (L.kind == K_CONV3) {
     a.mode = CM_CONV3;
     a.up = 1;
@@ -322,11 +343,6 @@ hipError_t conv_wgrad(lshom_cnn* c, const Plan& p, const Layer& L, View in, int 
   hipError_t e = launch_wgrad(a, splits, c->stream);
   if (e != hipSuccess) return e;
   return launch_wgrad_reduce(partial, splits, a.rows, L.np, c->g + L.w_off, c->g + L.b_off, c->stream);
-}
-
-hipError_t prep(lshom_cnn* c, long long P, int C, int Cp, const float* g0, int ld0, const float* g1, int ld1,
-                const bf16_t* act, int lda, bf16_t* gpre) {
-  return launch_grad_prep(P, C, Cp, g0, ld0, g1, ld1, act, lda, gpre, c->stream);
 }
 
 hipError_t cast_all(lshom_cnn* c) {
@@ -409,97 +425,96 @@ hipError_t backward(lshom_cnn* c, const Plan& p, int B) {
   hipError_t e;
 #define BWD(expr)                          \
   if ((e = (expr)) != hipSuccess) return e
-  bf16_t* gpre = at<bf16_t>(c, p.gpre);
-  float* gA = at<float>(c, p.gA);
-  float* gB = at<float>(c, p.gB);
-  float* dcat0 = at<float>(c, p.dcat0);
-  float* dcat1 = at<float>(c, p.dcat1);
-  float* dcat2 = at<float>(c, p.dcat2);
+  // the operand of the current layer and the one of the layer before it
+  bf16_t* cur = at<bf16_t>(c, p.gpre);
+  bf16_t* nxt = at<bf16_t>(c, p.gpre2);
+  float* fine = at<float>(c, p.gA);
+  float* skip0 = at<float>(c, p.skip0);
+  float* skip1 = at<float>(c, p.skip1);
+  float* skip2 = at<float>(c, p.skip2);
   bf16_t* cat0 = at<bf16_t>(c, p.cat0);
   bf16_t* cat1 = at<bf16_t>(c, p.cat1);
   bf16_t* cat2 = at<bf16_t>(c, p.cat2);
   auto A = [&](size_t off) { return at<bf16_t>(c, off); };
+  // input gradient of L through the ReLU of act (C channels), which becomes
+  // the current operand; skip: the FP32 gradient of the channels beyond C
+  auto dgrad = [&](const Layer& L, int Hout, const bf16_t* act, int lda, int C, const float* add = nullptr,
+                   float* skip = nullptr) {
+    const hipError_t er = conv_dgrad(c, L, cur, B, Hout, skip, GradNext{act, lda, add, add ? C : 0, C, nxt});
+    std::swap(cur, nxt);
+    return er;
+  };
 
-  // head (no ReLU)
-  {
-    const Layer& L = layer(c, "head");
-    BWD(prep(c, P[0], 2, L.np, at<float>(c, p.gout), 2, nullptr, 0, nullptr, 0, gpre));
-    BWD(conv_wgrad(c, p, L, View{A(p.dec0b), c0, c0}, B, Nl[0], Nl[0], CM_POINT, 1, gpre));
-    BWD(conv_dgrad(c, L, gpre, B, Nl[0], gA));
-  }
-  // one decoder level: dec_b, dec_a, up; returns the coarse gradient in gB
+  // one decoder level: dec_b, dec_a, up
   struct Lev {
     const char *b, *a, *up;
     size_t act_b, act_a, coarse_in;
     bf16_t* cat;
-    float* dcat;
+    float* skip;
     int l;
   };
-  const Lev levs[3] = {{"dec0b", "dec0a", "up0", p.dec0b, p.dec0a, p.dec1b, cat0, dcat0, 0},
-                       {"dec1b", "dec1a", "up1", p.dec1b, p.dec1a, p.dec2b, cat1, dcat1, 1},
-                       {"dec2b", "dec2a", "up2", p.dec2b, p.dec2a, p.botb, cat2, dcat2, 2}};
+  const Lev levs[3] = {{"dec0b", "dec0a", "up0", p.dec0b, p.dec0a, p.dec1b, cat0, skip0, 0},
+                       {"dec1b", "dec1a", "up1", p.dec1b, p.dec1a, p.dec2b, cat1, skip1, 1},
+                       {"dec2b", "dec2a", "up2", p.dec2b, p.dec2a, p.botb, cat2, skip2, 2}};
+  // head (no ReLU)
+  {
+    const Layer& L = layer(c, "head");
+    BWD(launch_grad_prep(P[0], 2, L.np, at<float>(c, p.gout), 2, cur, c->stream));
+    BWD(conv_wgrad(c, p, L, View{A(p.dec0b), c0, c0}, B, Nl[0], Nl[0], CM_POINT, 1, cur));
+    BWD(dgrad(L, Nl[0], A(p.dec0b), c0, c0));
+  }
   for (const Lev& lv : levs) {
     const int l = lv.l;
     const int C = c0 << l;  // channels of this level
-    // gradient of dec_b output is in gA (level 0) or gB (after a pool)
-    float* g_in = l == 0 ? gA : gB;
     const Layer& Lb = layer(c, lv.b);
-    BWD(prep(c, P[l], C, Lb.np, g_in, C, nullptr, 0, A(lv.act_b), C, gpre));
-    BWD(conv_wgrad(c, p, Lb, View{A(lv.act_a), C, C}, B, Nl[l], Nl[l], CM_CONV3, 1, gpre));
-    float* g_a = l == 0 ? gB : gA;
-    BWD(conv_dgrad(c, Lb, gpre, B, Nl[l], g_a));
+    BWD(conv_wgrad(c, p, Lb, View{A(lv.act_a), C, C}, B, Nl[l], Nl[l], CM_CONV3, 1, cur));
+    BWD(dgrad(Lb, Nl[l], A(lv.act_a), C, C));
     const Layer& La = layer(c, lv.a);
-    BWD(prep(c, P[l], C, La.np, g_a, C, nullptr, 0, A(lv.act_a), C, gpre));
-    BWD(conv_wgrad(c, p, La, View{lv.cat, 2 * C, 2 * C}, B, Nl[l], Nl[l], CM_CONV3, 1, gpre));
-    BWD(conv_dgrad(c, La, gpre, B, Nl[l], lv.dcat));
-    // up-convolution: output channels [0, C) of the concat buffer
+    BWD(conv_wgrad(c, p, La, View{lv.cat, 2 * C, 2 * C}, B, Nl[l], Nl[l], CM_CONV3, 1, cur));
+    // channels [0, C) of the concat buffer are the up-convolution's output,
+    // the others the skip connection
+    BWD(dgrad(La, Nl[l], lv.cat, 2 * C, C, nullptr, lv.skip));
     const Layer& Lu = layer(c, lv.up);
-    BWD(prep(c, P[l], C, Lu.np, lv.dcat, 2 * C, nullptr, 0, lv.cat, 2 * C, gpre));
-    BWD(conv_wgrad(c, p, Lu, View{A(lv.coarse_in), 2 * C, 2 * C}, B, Nl[l + 1], Nl[l], CM_CONV3, 3, gpre));
-    BWD(conv_dgrad(c, Lu, gpre, B, Nl[l], gA));  // fine-grid gradient of the upsampled input
-    BWD(launch_pool3_sum(B, Nl[l + 1], Nl[l + 1], 2 * C, gA, gB, c->stream));
+    BWD(conv_wgrad(c, p, Lu, View{A(lv.coarse_in), 2 * C, 2 * C}, B, Nl[l + 1], Nl[l], CM_CONV3, 3, cur));
+    BWD(conv_dgrad(c, Lu, cur, B, Nl[l], fine));  // fine-grid gradient of the upsampled input
+    BWD(launch_pool3_sum(B, Nl[l + 1], Nl[l + 1], 2 * C, fine, nullptr, A(lv.coarse_in), nxt, c->stream));
+    std::swap(cur, nxt);
   }
-  // bottom: gradient of bot_b output in gB
+  // bottom
   {
     const int C = 8 * c0;
     const Layer& Lb = layer(c, "bot_b");
-    BWD(prep(c, P[3], C, Lb.np, gB, C, nullptr, 0, A(p.botb), C, gpre));
-    BWD(conv_wgrad(c, p, Lb, View{A(p.bota), C, C}, B, Nl[3], Nl[3], CM_CONV3, 1, gpre));
-    BWD(conv_dgrad(c, Lb, gpre, B, Nl[3], gA));
+    BWD(conv_wgrad(c, p, Lb, View{A(p.bota), C, C}, B, Nl[3], Nl[3], CM_CONV3, 1, cur));
+    BWD(dgrad(Lb, Nl[3], A(p.bota), C, C));
     const Layer& La = layer(c, "bot_a");
-    BWD(prep(c, P[3], C, La.np, gA, C, nullptr, 0, A(p.bota), C, gpre));
-    BWD(conv_wgrad(c, p, La, View{A(p.down2), C, C}, B, Nl[3], Nl[3], CM_CONV3, 1, gpre));
-    BWD(conv_dgrad(c, La, gpre, B, Nl[3], gB));
+    BWD(conv_wgrad(c, p, La, View{A(p.down2), C, C}, B, Nl[3], Nl[3], CM_CONV3, 1, cur));
+    BWD(dgrad(La, Nl[3], A(p.down2), C, C));
   }
-  // encoder levels 2, 1, 0: gradient of down_l output in gB
+  // encoder levels 2, 1, 0
   struct Enc {
     const char *down, *b, *a;
-    size_t act_down, act_a, in_a;
+    size_t act_a, in_a;
     bf16_t* cat;
-    float* dcat;
+    const float* skip;
     int l;
   };
-  const Enc encs[3] = {{"down2", "enc2b", "enc2a", p.down2, p.enc2a, p.down1, cat2, dcat2, 2},
-                       {"down1", "enc1b", "enc1a", p.down1, p.enc1a, p.down0, cat1, dcat1, 1},
-                       {"down0", "enc0b", "enc0a", p.down0, p.enc0a, p.x, cat0, dcat0, 0}};
+  const Enc encs[3] = {{"down2", "enc2b", "enc2a", p.enc2a, p.down1, cat2, skip2, 2},
+                       {"down1", "enc1b", "enc1a", p.enc1a, p.down0, cat1, skip1, 1},
+                       {"down0", "enc0b", "enc0a", p.enc0a, p.x, cat0, skip0, 0}};
   for (const Enc& en : encs) {
     const int l = en.l;
     const int C = c0 << l;      // channels of level l
-    const int Cd = 2 * C;       // channels of the down output
     const Layer& Ld = layer(c, en.down);
-    BWD(prep(c, P[l + 1], Cd, Ld.np, gB, Cd, nullptr, 0, A(en.act_down), Cd, gpre));
-    BWD(conv_wgrad(c, p, Ld, View{en.cat + C, C, 2 * C}, B, Nl[l], Nl[l + 1], CM_DOWN3, 1, gpre));
-    BWD(conv_dgrad(c, Ld, gpre, B, Nl[l + 1], gA));  // fine grid [P_l][C]
+    BWD(conv_wgrad(c, p, Ld, View{en.cat + C, C, 2 * C}, B, Nl[l], Nl[l + 1], CM_DOWN3, 1, cur));
     // enc_b output = skip: gradient from the down path plus the concat slice
+    BWD(dgrad(Ld, Nl[l + 1], en.cat + C, 2 * C, C, en.skip));
     const Layer& Lb = layer(c, en.b);
-    BWD(prep(c, P[l], C, Lb.np, gA, C, en.dcat + C, 2 * C, en.cat + C, 2 * C, gpre));
-    BWD(conv_wgrad(c, p, Lb, View{A(en.act_a), C, C}, B, Nl[l], Nl[l], CM_CONV3, 1, gpre));
-    BWD(conv_dgrad(c, Lb, gpre, B, Nl[l], gB));
+    BWD(conv_wgrad(c, p, Lb, View{A(en.act_a), C, C}, B, Nl[l], Nl[l], CM_CONV3, 1, cur));
+    BWD(dgrad(Lb, Nl[l], A(en.act_a), C, C));
     const Layer& La = layer(c, en.a);
-    BWD(prep(c, P[l], C, La.np, gB, C, nullptr, 0, A(en.act_a), C, gpre));
     const int cin_a = l == 0 ? 8 : C;
-    BWD(conv_wgrad(c, p, La, View{A(en.in_a), cin_a, cin_a}, B, Nl[l], Nl[l], CM_CONV3, 1, gpre));
-    if (l > 0) BWD(conv_dgrad(c, La, gpre, B, Nl[l], gB));  // gradient of down_{l-1} output
+    BWD(conv_wgrad(c, p, La, View{A(en.in_a), cin_a, cin_a}, B, Nl[l], Nl[l], CM_CONV3, 1, cur));
+    if (l > 0) BWD(dgrad(La, Nl[l], A(en.in_a), C, C));  // through down_{l-1}
   }
 #undef BWD
   return hipSuccess;
@@ -761,7 +776,7 @@ lshom_status lshom_cnn_layer_dgrad(lshom_cnn* c, int layer, const uint16_t* gy_d
     // of the upsampling (sum over each 3 x 3 block)
     float* fine = at<float>(c, p.gA);
     CNN_TRY(c, conv_dgrad(c, L, gy_dev, c->ws_B, gm.Ho, fine));
-    CNN_TRY(c, launch_pool3_sum(c->ws_B, gm.Hi, gm.Hi, L.cin, fine, gx_dev, c->stream));
+    CNN_TRY(c, launch_pool3_sum(c->ws_B, gm.Hi, gm.Hi, L.cin, fine, gx_dev, nullptr, nullptr, c->stream));
   } else {
     CNN_TRY(c, conv_dgrad(c, L, gy_dev, c->ws_B, gm.Ho, gx_dev));
   }

@@ -39,7 +39,15 @@ struct ConvArgs {
   int ldb;
   float* out_f;          // FP32 output (or null): pixel stride ldf
   int ldf;
-  int wide_b, wide_f;    // 16-byte stores fit the output's base and stride (set by the launcher)
+  // Input gradients (mask given): channels below n_b leave as the next layer's
+  // operand, bf16((value + add) where mask > 0, else 0) in out_b; the others
+  // in FP32 as channels 0, 1, .. of out_f.
+  const bf16_t* mask;    // activation whose ReLU the gradient passes, or null: pixel stride ldm
+  int ldm;
+  const float* add;      // second gradient of the activation, or null: pixel stride lda
+  int lda;
+  int n_b;               // a multiple of 8
+  int wide_b, wide_f, wide_m;  // 16-byte accesses fit the base and stride (set by the launcher)
   FastDiv fd_chunks;     // C0 / 8 (set by the launcher)
 };
 
@@ -76,12 +84,12 @@ hipError_t launch_wgrad(const WgradArgs& a, int splits, hipStream_t s);
 hipError_t launch_wgrad_reduce(const float* partial, int splits, int rows, int Np, float* grad_w, float* grad_b,
                                hipStream_t s);
 
-// gpre[p][c] = bf16((g0[p * ld0 + c] + g1[p * ld1 + c]) * mask), c < C, zero
-// for C <= c < Cp; mask = act[p * lda + c] > 0 when act is given.
-hipError_t launch_grad_prep(long long P, int C, int Cp, const float* g0, int ld0, const float* g1, int ld1,
-                            const bf16_t* act, int lda, bf16_t* gpre, hipStream_t s);
-// coarse[b, I, J, c] (+)= sum over the 3 x 3 fine pixels of fine[b, 3I+p, 3J+q, c]
-hipError_t launch_pool3_sum(int B, int Hc, int Wc, int C, const float* fine, float* coarse, hipStream_t s);
+// gpre[p][c] = bf16(g[p * ld + c]), c < C, zero for C <= c < Cp.
+hipError_t launch_grad_prep(long long P, int C, int Cp, const float* g, int ld, bf16_t* gpre, hipStream_t s);
+// coarse[b, I, J, c] = sum over the 3 x 3 fine pixels of fine[b, 3I+p, 3J+q, c];
+// with act [B, Hc, Wc, C] the sum where act > 0, else 0, as bf16 in coarse_b.
+hipError_t launch_pool3_sum(int B, int Hc, int Wc, int C, const float* fine, float* coarse, const bf16_t* act,
+                            bf16_t* coarse_b, hipStream_t s);
 // Network input [B, N, N, 8]: phase indicator (phase != 0), log10(rho) / 4, zeros.
 // transpose: read the image transposed (load case E = e2).  scale 3: the
 // image is 3N x 3N and pixel (i, j) is the majority of block (3i.., 3j..).

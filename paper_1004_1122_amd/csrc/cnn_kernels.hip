@@ -46,7 +46,37 @@ __device__ __forceinline__ void conv_store(const ConvArgs& a, long long op, int 
     v[e] = (e < 4 ? lo[e & 3] : hi[e & 3]) + bias[e];
     if (a.relu) v[e] = fmaxf(v[e], 0.f);
   }
-  if (a.out_b) {
+  bool to_b = a.out_b != nullptr, to_f = a.out_f != nullptr;
+  int nf = n;
+  if (a.mask) {
+    to_b = n < a.n_b;
+    to_f = !to_b;
+    nf = n - a.n_b;
+    if (to_b) {
+      const long long om = op * a.ldm + n, oa = op * a.lda + n;
+      const bool all = n + 8 <= a.N;
+      bf16_t m[8];
+      float w[8];
+      if (all && a.wide_m) {
+        const uint4 q = *reinterpret_cast<const uint4*>(a.mask + om);
+        const uint32_t qw[4] = {q.x, q.y, q.z, q.w};
+#pragma unroll
+        for (int e = 0; e < 8; ++e) m[e] = (bf16_t)(qw[e >> 1] >> (16 * (e & 1)));
+      } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) m[e] = n + e < a.N ? a.mask[om + e] : (bf16_t)0;
+      }
+      if (a.add) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) w[e] = n + e < a.N ? a.add[oa + e] : 0.f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] += w[e];
+      }
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[e] = bf2f(m[e]) > 0.f ? v[e] : 0.f;
+    }
+  }
+  if (to_b) {
     bf16_t* o = a.out_b + op * a.ldb + n;
     if (n + 8 <= a.N && a.wide_b) {
       uint4 w;
@@ -61,8 +91,8 @@ __device__ __forceinline__ void conv_store(const ConvArgs& a, long long op, int 
         if (n + e < a.N) o[e] = f2bf(v[e]);
     }
   }
-  if (a.out_f) {
-    float* o = a.out_f + op * a.ldf + n;
+  if (to_f) {
+    float* o = a.out_f + op * a.ldf + nf;
     if (n + 8 <= a.N && a.wide_f) {
       *reinterpret_cast<float4_t*>(o) = float4_t{v[0], v[1], v[2], v[3]};
       *reinterpret_cast<float4_t*>(o + 4) = float4_t{v[4], v[5], v[6], v[7]};
@@ -668,23 +698,17 @@ __global__ __launch_bounds__(256) void wgrad_reduce_kernel(const float* partial,
   }
 }
 
-__global__ void grad_prep_kernel(long long P, int C, int Cp, const float* g0, int ld0, const float* g1, int ld1,
-                                 const bf16_t* act, int lda, bf16_t* gpre) {
+__global__ void grad_prep_kernel(long long P, int C, int Cp, const float* g, int ld, bf16_t* gpre) {
   const long long n = P * Cp;
   for (long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (long long)gridDim.x * blockDim.x) {
     const long long p = e / Cp;
     const int c = (int)(e - p * Cp);
-    float v = 0.f;
-    if (c < C) {
-      v = g0[p * ld0 + c];
-      if (g1) v += g1[p * ld1 + c];
-      if (act && !(bf2f(act[p * lda + c]) > 0.f)) v = 0.f;
-    }
-    gpre[e] = f2bf(v);
+    gpre[e] = f2bf(c < C ? g[p * ld + c] : 0.f);
   }
 }
 
-__global__ void pool3_sum_kernel(int B, int Hc, int Wc, int C, const float* fine, float* coarse) {
+__global__ void pool3_sum_kernel(int B, int Hc, int Wc, int C, const float* fine, float* coarse, const bf16_t* act,
+                                 bf16_t* coarse_b) {
   const long long n = (long long)B * Hc * Wc * C;
   for (long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (long long)gridDim.x * blockDim.x) {
     const int c = (int)(e % C);
@@ -697,7 +721,8 @@ __global__ void pool3_sum_kernel(int B, int Hc, int Wc, int C, const float* fine
     for (int p = 0; p < 3; ++p)
       for (int q = 0; q < 3; ++q)
         s += fine[(((long long)b * 3 * Hc + 3 * I + p) * (3LL * Wc) + 3 * J + q) * C + c];
-    coarse[e] = s;
+    if (act) coarse_b[e] = f2bf(bf2f(act[e]) > 0.f ? s : 0.f);
+    else coarse[e] = s;
   }
 }
 
@@ -914,6 +939,7 @@ hipError_t launch_conv(const ConvArgs& in, hipStream_t s) {
   ConvArgs a = in;
   a.wide_b = a.ldb % 8 == 0 && (reinterpret_cast<uintptr_t>(a.out_b) & 15u) == 0;
   a.wide_f = a.ldf % 4 == 0 && (reinterpret_cast<uintptr_t>(a.out_f) & 15u) == 0;
+  a.wide_m = a.ldm % 8 == 0 && (reinterpret_cast<uintptr_t>(a.mask) & 15u) == 0;
   a.fd_chunks = make_fastdiv((uint32_t)a.C0 / 8u);
   if (a.mode == CM_CONV3 && a.Wo >= kConvTileSide) {
     // eight rows a block while two blocks fit a CU (the patch's two extra rows
@@ -954,16 +980,15 @@ hipError_t launch_wgrad_reduce(const float* partial, int splits, int rows, int N
   return hipGetLastError();
 }
 
-hipError_t launch_grad_prep(long long P, int C, int Cp, const float* g0, int ld0, const float* g1, int ld1,
-                            const bf16_t* act, int lda, bf16_t* gpre, hipStream_t s) {
-  hipLaunchKernelGGL(grad_prep_kernel, dim3(grid_for(P * Cp)), dim3(256), 0, s, P, C, Cp, g0, ld0, g1, ld1, act, lda,
-                     gpre);
+hipError_t launch_grad_prep(long long P, int C, int Cp, const float* g, int ld, bf16_t* gpre, hipStream_t s) {
+  hipLaunchKernelGGL(grad_prep_kernel, dim3(grid_for(P * Cp)), dim3(256), 0, s, P, C, Cp, g, ld, gpre);
   return hipGetLastError();
 }
 
-hipError_t launch_pool3_sum(int B, int Hc, int Wc, int C, const float* fine, float* coarse, hipStream_t s) {
+hipError_t launch_pool3_sum(int B, int Hc, int Wc, int C, const float* fine, float* coarse, const bf16_t* act,
+                            bf16_t* coarse_b, hipStream_t s) {
   hipLaunchKernelGGL(pool3_sum_kernel, dim3(grid_for((long long)B * Hc * Wc * C)), dim3(256), 0, s, B, Hc, Wc, C, fine,
-                     coarse);
+                     coarse, act, coarse_b);
   return hipGetLastError();
 }
 
