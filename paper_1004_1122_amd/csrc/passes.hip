@@ -224,6 +224,7 @@ __global__ __launch_bounds__(NT) void row_kernel(RowArgs<T> a) {
   off = align16(off + (size_t)R * n);
   T* cond = reinterpret_cast<T*>(smem_raw + off);
   const int tid = threadIdx.x;
+  constexpr int kNV = 256 / NT;  // shares of the block sums per thread
   const long long row0 = rb * R;
   const int rows_here = (int)((a.nrows - row0) < R ? (a.nrows - row0) : R);
   // phase bytes of this block's rows (each read once, coalesced)
@@ -363,7 +364,17 @@ __global__ __launch_bounds__(NT) void row_kernel(RowArgs<T> a) {
     fft_lds<T, +1, NT, RS>(Z, npairs, ss, a.plan, tw, tid);
 
     if constexpr (MODE == ROW_INV) {
-      double acc[kMaxDim] = {0.0, 0.0, 0.0};
+      double acc[kMaxDim][kNV];
+#pragma unroll
+      for (int c = 0; c < kMaxDim; ++c)
+#pragma unroll
+        for (int q = 0; q < kNV; ++q) acc[c][q] = 0.0;
+      // x y onto the share of the block sums that element idx belongs to (a
+      // fused step for every block size: left to the compiler they differ)
+      auto add = [&](double (&s)[kNV], int idx, double x, double y) {
+        if (kNV == 1 || (idx & NT) == 0) s[0] = __builtin_fma(x, y, s[0]);
+        else s[kNV - 1] = __builtin_fma(x, y, s[kNV - 1]);
+      };
       if (a.tensor && (a.flags & (ROWF_LEFF | ROWF_DL_OUT))) {
         T shift[6], zero6[6];
         reference_shift(a, l0, shift);
@@ -402,7 +413,7 @@ __global__ __launch_bounds__(NT) void row_kernel(RowArgs<T> a) {
             if (a.flags & ROWF_LEFF) {
               tensor_times(cond, q, d, zero6, v, w);
 #pragma unroll
-              for (int c = 0; c < kMaxDim; ++c) acc[c] += (double)w[c];
+              for (int c = 0; c < kMaxDim; ++c) add(acc[c], idx, (double)w[c], 1.0);
             }
           }
         }
@@ -424,17 +435,19 @@ __global__ __launch_bounds__(NT) void row_kernel(RowArgs<T> a) {
           double* out = pe ? (pe->e_out ? pe->e_out + c * nvox : nullptr) : pick3(a.real_out, c);
           if (out) out[g] = val;
           if (a.flags & ROWF_LEFF) {
-            const double jv = (double)cond[ph[rl * n + x]] * val;
+            const double lam = (double)cond[ph[rl * n + x]];
 #pragma unroll
             for (int cc = 0; cc < kMaxDim; ++cc)
-              if (cc == c) acc[cc] += jv;
+              if (cc == c) add(acc[cc], idx, lam, val);
           }
         }
       }
       }
       if (a.flags & ROWF_LEFF) {
         double* dst = parts.region(PART_AUX) + (long long)bx * 3;
-        for (int c = 0; c < 3; ++c) store_partial<NT>(acc[c], dst + c);
+        double sum[3];
+        (void)block_sums_shared<NT, 3, kNV>(acc, sum, 0);
+        if (tid < 3) dst[tid] = tid == 0 ? sum[0] : (tid == 1 ? sum[1] : sum[2]);
       }
       return;
     }
@@ -522,6 +535,8 @@ __global__ __launch_bounds__(NT) void col_kernel(ColArgs<T> a) {
   // see flags that only earlier launches write
   constexpr bool kInv = MODE == COL_INV_C || MODE == COL_INV_C_GEN;
   constexpr bool kGen = MODE == COL_INV_C_GEN || MODE == COL_FWD_PROJ_GEN;
+  constexpr int kNV = 256 / NT;  // shares of the block sums per thread
+  static_assert(kBatch % kNV == 0, "a batch of elements covers every share");
   const bool pipe = kGen && a.pipe;
   const bool aniso = kGen && a.aniso;
   if (!(kInv && (a.cg_step || pipe)) && gated_out_stable(st, a.gate)) return;
@@ -559,8 +574,8 @@ __global__ __launch_bounds__(NT) void col_kernel(ColArgs<T> a) {
   if constexpr (kInv) {
     double beta = 0.0;
     if (pipe) {
-      if (!pipe_direction<NT>(st, parts, a.inv_n, a.gate, bx == 0)) return;
-    } else if (a.cg_step && !cg_direction<NT>(st, parts, a.inv_n, &beta, a.gate, a.eq, bx == 0)) {
+      if (!pipe_direction<NT, kNV>(st, parts, a.inv_n, a.gate, bx == 0)) return;
+    } else if (a.cg_step && !cg_direction<NT, kNV>(st, parts, a.inv_n, &beta, a.gate, a.eq, bx == 0)) {
       return;
     }
     const T tb = (T)beta;
@@ -681,7 +696,9 @@ __global__ __launch_bounds__(NT) void col_kernel(ColArgs<T> a) {
   } else {
   // COL_FWD_PROJ
   fft_lds<T, -1, NT, RS>(Z, nseq, ss, a.plan, tw, tid);
-  double acc = 0.0, acc_eq = 0.0;
+  double acc[2][kNV];  // dot product, equilibrium sum
+#pragma unroll
+  for (int q = 0; q < kNV; ++q) acc[0][q] = acc[1][q] = 0.0;
   const int n_last = a.nd[a.dims - 1];
   const int total = L * C;
   const T cs = a.coef_s * (a.s_inv_l0 ? (T)(1.0 / (pe ? pe->l0 : a.l0)) : T(1));
@@ -755,28 +772,24 @@ __global__ __launch_bounds__(NT) void col_kernel(ColArgs<T> a) {
         const uint32_t kl = (uint32_t)(i0 + c);
         const double w = half_weight(kl - fdiv(kl, a.fd_h) * (uint32_t)a.h, n_last);
         if (a.dot == 1) {
-          acc += w * ((double)b.re * (double)val.re + (double)b.im * (double)val.im);
+          acc[0][u % kNV] += w * ((double)b.re * (double)val.re + (double)b.im * (double)val.im);
         } else {
           // dot 2: |out|^2; dot 3: the step |out - base|^2 of the basic scheme
           const double dr = a.dot == 3 ? (double)val.re - (double)b.re : (double)val.re;
           const double di = a.dot == 3 ? (double)val.im - (double)b.im : (double)val.im;
           const double m2 = dr * dr + di * di;
-          acc += w * m2;
-          if (a.eq) acc_eq += w * k2 * m2;
+          acc[0][u % kNV] += w * m2;
+          if (a.eq) acc[1][u % kNV] += w * k2 * m2;
         }
       }
     }
   }
   if (a.dot) {
-    if (a.eq && a.dot != 1) {
-      double v[2] = {acc, acc_eq};
-      (void)block_sums_gated<NT, 2>(v, 0);
-      if (tid == 0) {
-        parts.region(a.dot_region)[bx] = v[0];
-        parts.region(a.eq_region)[bx] = v[1];
-      }
-    } else {
-      store_partial<NT>(acc, parts.region(a.dot_region) + bx);
+    double sum[2];
+    (void)block_sums_shared<NT, 2, kNV>(acc, sum, 0, a.eq && a.dot != 1 ? 2 : 1);
+    if (tid == 0) {
+      parts.region(a.dot_region)[bx] = sum[0];
+      if (a.eq && a.dot != 1) parts.region(a.eq_region)[bx] = sum[1];
     }
     if (a.dot_region == PART_RR0 && bx == 0 && tid == 0) st->nparts[0] = (int)gridDim.x;
     if (a.dot_region == PART_PQ && bx == 0 && tid == 0) st->nparts_pq = (int)gridDim.x;
@@ -1440,22 +1453,25 @@ long long update_blocks(long long n) {
   return b > kUpdateBlocks ? kUpdateBlocks : (b < 1 ? 1 : b);
 }
 
-// Block size: two waves where they hold the butterflies.  Four where more
-// than 128 butterflies of a heavy radix would give two waves a second round
-// that leaves one of them idle and LDS holds at most four blocks per CU, so
-// that there are too few waves to fill in (729^2, 162 butterflies of radix 9,
-// 38 KB: 22.9 / 28.6 / 21.5 us for the three passes with two waves, 18.2 /
-// 23.6 / 16.5 us with four; ten such problems 79 / 122 / 79 us and 63 / 96 / 62
-// us); with more blocks per CU two waves are the better (32 problems of 243^2
-// FP32, 3.9 KB: 15.2 us, with four 17.5 us).  The choice depends on the grid
-// alone, as it sets the order of the sums and a batch reproduces single
-// solves bit for bit.
-static int pick_threads(int points, const FftPlan& plan, size_t lds) {
+// Block size: two waves where they hold the butterflies, four
+// - where the launch has so few blocks that the chip has room for them and a
+//   block has more points than two waves have lanes (per iteration, FP64:
+//   360^2 51 -> 47 us, 625^2 80 -> 65 us, 60^3 85 -> 74 us; five problems of
+//   150^2 1.13 -> 1.10 ms, but twelve 1.32 -> 1.55 ms);
+// - where 160 or more butterflies of a heavy radix would give two waves a
+//   second round that leaves one of them idle, and the blocks a CU can hold
+//   are too few to fill in (twenty-four problems of 500^2 FP64, 200
+//   butterflies, 24 KB: 9.3 -> 8.8 ms; in FP32, 12 KB: 8.1 -> 8.6 ms).
+// With more blocks two waves are the better (32 problems of 243^2 FP32, 3.9 KB
+// a block: 15.2 us, with four 17.5 us).  The sums do not depend on the choice
+// (block_sums_shared), so a batch still reproduces single solves bit for bit.
+static int pick_threads(int points, const FftPlan& plan, size_t lds, long long blocks) {
   if (points > plan_batch_cap(plan, 128)) return 256;
   int heavy = 0;
   for (int s = 0; s < plan.nstages; ++s)
     if (plan.radix[s] >= 5) heavy = std::max(heavy, points / plan.radix[s]);
-  return heavy > 128 && 5 * lds > 160 * 1024 ? 256 : 128;
+  if (points > 128 && blocks <= 1024) return 256;
+  return heavy >= 160 && 7 * lds > 160 * 1024 ? 256 : 128;
 }
 
 // Largest phase index of each image (validation at workspace set-up): 16
@@ -1562,7 +1578,7 @@ hipError_t launch_row(const RowArgs<T>& a, hipStream_t s) {
   const int comps = a.split ? 1 : a.d;
   const size_t lds = row_lds_bytes(a.n, a.rows_per_block, comps, (int)sizeof(cx<T>), a.n_phases, nullptr);
   const long long nb = row_blocks(a);
-  const int nt = a.nt ? a.nt : pick_threads(comps * (a.rows_per_block / 2) * a.n, a.plan, lds);
+  const int nt = a.nt ? a.nt : pick_threads(comps * (a.rows_per_block / 2) * a.n, a.plan, lds, nb * nprob_of(a.bt));
   switch (plan_radix_set(a.plan)) {
     case RADIX_POW3: launch_row_rs<T, RADIX_POW3>(a, lds, nb, nt, s); break;
     case RADIX_POW2: launch_row_rs<T, RADIX_POW2>(a, lds, nb, nt, s); break;
@@ -1577,7 +1593,7 @@ hipError_t launch_col(const ColArgs<T>& a, hipStream_t s) {
   if (w2_col(a) && !a.pipe && (a.mode == COL_INV_C || a.mode == COL_FWD_PROJ)) return launch_w2_col(a, s);
   const size_t lds = col_lds_bytes(a.L, a.tile, a.d, (int)sizeof(cx<T>), nullptr);
   const long long nb = col_blocks(a);
-  const int nt = a.nt ? a.nt : pick_threads(a.d * a.tile * a.L, a.plan, lds);
+  const int nt = a.nt ? a.nt : pick_threads(a.d * a.tile * a.L, a.plan, lds, nb * nprob_of(a.bt));
   switch (plan_radix_set(a.plan)) {
     case RADIX_POW3: launch_col_rs<T, RADIX_POW3>(a, lds, nb, nt, s); break;
     case RADIX_POW2: launch_col_rs<T, RADIX_POW2>(a, lds, nb, nt, s); break;

@@ -131,6 +131,64 @@ __device__ __forceinline__ bool block_sums_gated(double (&v)[NS], int skip0) {
   return skip != 0;
 }
 
+// The same with NV = 1 or 2 shares per thread: the sums of a block of NT NV
+// threads, of which each thread here stands for NV (thread t for t and t + NT),
+// in the same order.  Kernels that run with 128 or 256 threads, as their launch
+// fills the chip, sum with 256 / NT shares: their results do not depend on the
+// block size, and a batch reproduces single solves bit for bit.  Two shares
+// cost no more than one: after the first exchange the halves of a wave carry
+// one share each.  Only the first n of the NS sums are formed.
+template <int NT, int NS, int NV>
+__device__ __forceinline__ bool block_sums_shared(const double (&v)[NS][NV], double (&sum)[NS], int skip0, int n = NS) {
+  static_assert(NV == 1 || NV == 2, "one or two shares");
+  __shared__ double red[NS][NV * NT / 64];
+  __shared__ double total[NS];
+  __shared__ int skip;
+  const int lane = threadIdx.x & 63;
+#pragma unroll
+  for (int s = 0; s < NS; ++s) {
+    if (s >= n) break;
+    double x = v[s][0];
+    if constexpr (NV == 2) {
+      const bool low = lane < 32;
+      x = (low ? v[s][0] : v[s][1]) + __shfl_xor(low ? v[s][1] : v[s][0], 32, 64);
+    } else {
+      x += __shfl_down(x, 32, 64);
+    }
+#pragma unroll
+    for (int off = 16; off > 0; off >>= 1) x += __shfl_down(x, off, 64);
+    if (lane % (64 / NV) == 0) red[s][(lane / 32) * (NT / 64) + (threadIdx.x >> 6)] = x;
+  }
+  if (threadIdx.x == 0) skip = skip0;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+      if (s >= n) break;
+      double t = 0.0;
+#pragma unroll
+      for (int i = 0; i < NV * NT / 64; ++i) t += red[s][i];
+      total[s] = t;
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int s = 0; s < NS; ++s) sum[s] = s < n ? total[s] : 0.0;
+  return skip != 0;
+}
+
+// This thread's NV shares of the sum of p[0..n) (see block_sums_shared).
+template <int NT, int NV>
+__device__ __forceinline__ void partial_shares(const double* p, int n, double (&share)[NV]) {
+#pragma unroll
+  for (int q = 0; q < NV; ++q) share[q] = 0.0;
+  for (int i = threadIdx.x; i < n; i += NT * NV) {
+#pragma unroll
+    for (int q = 0; q < NV; ++q)
+      if (q == 0 || i + q * NT < n) share[q] += p[i + q * NT];
+  }
+}
+
 // The two termination norms of Sec. 3 for iterate m: eta_r = l0 ||r|| / ||e0||
 // (Eq. (22)) from the real-space (r, r), and eta_e (Eq. (21)) from the
 // |k|^2-weighted spectral residual sum eq: for an admissible field the
@@ -173,15 +231,16 @@ __device__ inline bool equilibrium_test(DevState* st, int m, double rr, double e
 // without touching the state.
 // With eq (plain FP64 CG only) the equilibrium sums of the same producer are
 // summed too and the test follows the state's norm.
-template <int NT>
+template <int NT, int NV = 1>
 __device__ bool cg_direction(DevState* st, const Partials& parts, double inv_n, double* beta_out, int gate,
                              int eq, bool lead_block) {
   const int skip0 = gate_flags(st, gate);
   const int k = st->iter_a;
-  double v[3] = {partial_share<NT>(parts.region(k & 1), st->nparts[k & 1]),
-                 k > 0 ? partial_share<NT>(parts.region((k + 1) & 1), st->nparts[(k + 1) & 1]) : 0.0,
-                 eq ? partial_share<NT>(parts.region(PART_EQ0 + (k & 1)), st->nparts[k & 1]) : 0.0};
-  if (block_sums_gated<NT, 3>(v, skip0)) return false;
+  double share[3][NV], v[3];
+  partial_shares<NT, NV>(parts.region(k & 1), st->nparts[k & 1], share[0]);
+  partial_shares<NT, NV>(parts.region((k + 1) & 1), k > 0 ? st->nparts[(k + 1) & 1] : 0, share[1]);
+  partial_shares<NT, NV>(parts.region(PART_EQ0 + (k & 1)), eq ? st->nparts[k & 1] : 0, share[2]);
+  if (block_sums_shared<NT, 3, NV>(share, v, skip0, eq ? 3 : 2)) return false;
   const double rr = v[0] * inv_n;
   const double rr_prev = v[1] * inv_n;
   const bool lead = lead_block && threadIdx.x == 0;
@@ -230,14 +289,15 @@ __device__ bool cg_direction(DevState* st, const Partials& parts, double inv_n, 
 // block reads a value the lead block writes in this launch.  The lead block
 // (lead_block) records alpha and beta at parity k for the later passes of
 // the iteration.
-template <int NT>
+template <int NT, int NV = 1>
 __device__ bool pipe_direction(DevState* st, const Partials& parts, double inv_n, int gate, bool lead_block) {
   const int skip0 = gate_flags(st, gate);
   const int k = st->iter_a;
-  double v[3] = {partial_share<NT>(parts.region(k & 1), st->nparts[k & 1]),
-                 partial_share<NT>(parts.region(PART_PQ), st->nparts_pq),
-                 k > 0 ? partial_share<NT>(parts.region((k + 1) & 1), st->nparts[(k + 1) & 1]) : 0.0};
-  if (block_sums_gated<NT, 3>(v, skip0)) return false;
+  double share[3][NV], v[3];
+  partial_shares<NT, NV>(parts.region(k & 1), st->nparts[k & 1], share[0]);
+  partial_shares<NT, NV>(parts.region(PART_PQ), st->nparts_pq, share[1]);
+  partial_shares<NT, NV>(parts.region((k + 1) & 1), k > 0 ? st->nparts[(k + 1) & 1] : 0, share[2]);
+  if (block_sums_shared<NT, 3, NV>(share, v, skip0)) return false;
   const double gamma = v[0] * inv_n;
   const double delta = v[1] * inv_n;
   const double gamma_prev = v[2] * inv_n;
