@@ -23,7 +23,7 @@ struct Layer {
   std::string name;
   int kind;
   int cin;        // channels the kernel reads (input layer: 8, two of them real)
-  int cin_real;   // channels of the compact parameter order
+  int cin_real;   // channels of the parameter arrays
   int cout;       // real output channels
   int np;         // output channels padded to a multiple of 8
   int taps;
@@ -31,7 +31,7 @@ struct Layer {
   size_t f_off, t_off;  // offsets (elements) of the layer's tiles in w16 and wt16
 };
 
-constexpr size_t kAlignEl = 64;  // parameter blocks start on 256-byte boundaries
+constexpr size_t kAlignEl = 64;  // parameter arrays start on 256-byte boundaries
 size_t align_el(size_t v) { return (v + kAlignEl - 1) / kAlignEl * kAlignEl; }
 size_t align_b(size_t v) { return (v + 255) / 256 * 256; }
 int pad8(int c) { return (c + 7) / 8 * 8; }
@@ -45,9 +45,9 @@ struct lshom_cnn {
   std::string err;
   int c0 = 32;
   std::vector<Layer> layers;
-  size_t n_el = 0;         // elements per parameter array (padded layout)
+  size_t n_el = 0;         // elements per parameter array: n_compact, aligned
   size_t n_f = 0, n_t = 0; // elements of the bfloat16 copies w16 and wt16
-  long long n_compact = 0;
+  long long n_compact = 0; // parameters, in the order of the host arrays
   // parameter buffer
   char* pbuf = nullptr;
   size_t pbytes = 0;
@@ -118,20 +118,17 @@ void build_layers(lshom_cnn* c) {
   }
   add("head", K_CONV1, w[0], w[0], 2);
   size_t off = 0;
-  long long compact = 0;
   for (Layer& L : c->layers) {
     L.w_off = off;
-    off = align_el(off + (size_t)L.taps * L.cin * L.np);
-    L.b_off = off;
-    off = align_el(off + (size_t)L.np);
-    compact += (long long)L.taps * L.cin_real * L.cout + L.cout;
+    L.b_off = off + (size_t)L.taps * L.cin_real * L.cout;
+    off = L.b_off + (size_t)L.cout;
     L.f_off = c->n_f;
     c->n_f += (size_t)weight_tiles_fwd(L.taps, L.cin, L.np).elements();
     L.t_off = c->n_t;
     c->n_t += (size_t)weight_tiles_grad(L.taps, L.cin, L.np, L.kind == K_DOWN3).elements();
   }
-  c->n_el = off;
-  c->n_compact = compact;
+  c->n_compact = (long long)off;
+  c->n_el = align_el(off);
 }
 
 const Layer& layer(const lshom_cnn* c, const char* name) {
@@ -342,17 +339,31 @@ hipError_t conv_wgrad(lshom_cnn* c, const Plan& p, const Layer& L, View in, int 
   a.partial = partial;
   hipError_t e = launch_wgrad(a, splits, c->stream);
   if (e != hipSuccess) return e;
-  return launch_wgrad_reduce(partial, splits, a.rows, L.np, c->g + L.w_off, c->g + L.b_off, c->stream);
+  return launch_wgrad_reduce(partial, splits, a.rows, L.np, L.cin, L.cin_real, L.cout, c->g + L.w_off, c->g + L.b_off,
+                             c->stream);
 }
 
 hipError_t cast_all(lshom_cnn* c) {
+  CastArgs a{};
+  a.w = c->w;
+  a.w16 = c->w16;
+  a.wt16 = c->wt16;
   for (const Layer& L : c->layers) {
-    hipError_t e = launch_cast_weights(c->w + L.w_off, L.taps, L.cin, L.np, L.kind == K_CONV3 ? 1 : 0,
-                                       L.kind == K_DOWN3 ? 1 : 0, c->w16 + L.f_off, c->wt16 + L.t_off, c->stream);
-    if (e != hipSuccess) return e;
-    // bias copies are read in FP32; nothing to cast
+    if (a.layers == kCastLayers) return hipErrorInvalidValue;
+    CastLayer& q = a.layer[a.layers++];
+    q.w_off = (long long)L.w_off;
+    q.f_off = (long long)L.f_off;
+    q.t_off = (long long)L.t_off;
+    q.taps = L.taps;
+    q.cin = L.cin;
+    q.cin_real = L.cin_real;
+    q.cout = L.cout;
+    q.np = L.np;
+    q.flip = L.kind == K_CONV3 ? 1 : 0;
+    q.tap_pad = L.kind == K_DOWN3 ? 1 : 0;
   }
-  return hipSuccess;
+  // biases are read in FP32; nothing to cast
+  return launch_cast_weights(a, c->stream);
 }
 
 // --- forward and backward ----------------------------------------------------
@@ -627,17 +638,9 @@ lshom_status lshom_cnn_set_params(lshom_cnn* c, const float* host, int64_t n) {
   if (!c || !host) return LSHOM_ERR_INVALID_ARG;
   if (!c->pbuf) return fail(c, LSHOM_ERR_STATE, "parameter buffer not set");
   if (n != c->n_compact) return fail(c, LSHOM_ERR_INVALID_ARG, "parameter count mismatch");
-  std::vector<float> padded(c->n_el, 0.f);
-  long long k = 0;
-  for (const Layer& L : c->layers) {
-    for (int t = 0; t < L.taps; ++t)
-      for (int ci = 0; ci < L.cin_real; ++ci)
-        for (int o = 0; o < L.cout; ++o) padded[L.w_off + ((size_t)t * L.cin + ci) * L.np + o] = host[k++];
-    for (int o = 0; o < L.cout; ++o) padded[L.b_off + o] = host[k++];
-  }
   DeviceGuard g(c->device);
   CNN_TRY(c, order_after_user(c));
-  CNN_TRY(c, hipMemcpyAsync(c->w, padded.data(), c->n_el * 4, hipMemcpyHostToDevice, c->stream));
+  CNN_TRY(c, hipMemcpyAsync(c->w, host, (size_t)n * 4, hipMemcpyHostToDevice, c->stream));
   CNN_TRY(c, launch_fill_f32(c->g, (long long)c->n_el, 0.f, c->stream));
   CNN_TRY(c, launch_fill_f32(c->m, (long long)c->n_el, 0.f, c->stream));
   CNN_TRY(c, launch_fill_f32(c->v, (long long)c->n_el, 0.f, c->stream));
@@ -652,18 +655,10 @@ static lshom_status get_compact(lshom_cnn* c, const float* dev, float* host, int
   if (!c || !host) return LSHOM_ERR_INVALID_ARG;
   if (!c->params_set) return fail(c, LSHOM_ERR_STATE, "parameters not set");
   if (n != c->n_compact) return fail(c, LSHOM_ERR_INVALID_ARG, "parameter count mismatch");
-  std::vector<float> padded(c->n_el);
   DeviceGuard g(c->device);
   CNN_TRY(c, order_after_user(c));
-  CNN_TRY(c, hipMemcpyAsync(padded.data(), dev, c->n_el * 4, hipMemcpyDeviceToHost, c->stream));
+  CNN_TRY(c, hipMemcpyAsync(host, dev, (size_t)n * 4, hipMemcpyDeviceToHost, c->stream));
   CNN_TRY(c, hipStreamSynchronize(c->stream));
-  long long k = 0;
-  for (const Layer& L : c->layers) {
-    for (int t = 0; t < L.taps; ++t)
-      for (int ci = 0; ci < L.cin_real; ++ci)
-        for (int o = 0; o < L.cout; ++o) host[k++] = padded[L.w_off + ((size_t)t * L.cin + ci) * L.np + o];
-    for (int o = 0; o < L.cout; ++o) host[k++] = padded[L.b_off + o];
-  }
   return LSHOM_OK;
 }
 
@@ -733,7 +728,7 @@ lshom_status lshom_cnn_train_step(lshom_cnn* c, const uint8_t* phase_dev, const 
     const float b1 = 0.9f, b2 = 0.999f;
     const float c1 = 1.f - std::pow(b1, (float)c->adam_t);
     const float c2 = 1.f - std::pow(b2, (float)c->adam_t);
-    CNN_TRY(c, launch_adam((long long)c->n_el, c->w, c->g, c->m, c->v, lr, b1, b2, 1e-8f, c1, c2, c->stream));
+    CNN_TRY(c, launch_adam(c->n_compact, c->w, c->g, c->m, c->v, lr, b1, b2, 1e-8f, c1, c2, c->stream));
     CNN_TRY(c, cast_all(c));
   }
   double h = 0.0;

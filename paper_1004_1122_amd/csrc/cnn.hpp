@@ -80,9 +80,11 @@ inline int wgrad_splits(long long pixels, int rows, int Np) {
 
 hipError_t launch_conv(const ConvArgs& a, hipStream_t s);
 hipError_t launch_wgrad(const WgradArgs& a, int splits, hipStream_t s);
-// grad[r][n] = sum_s partial[s][r][n] for r < rows (fixed order).
-hipError_t launch_wgrad_reduce(const float* partial, int splits, int rows, int Np, float* grad_w, float* grad_b,
-                               hipStream_t s);
+// grad[r][n] = sum_s partial[s][r][n] for r < rows (fixed order); row r = t cin
+// + c goes to grad_w[(t cin_real + c) cout + n] where c < cin_real and n < cout,
+// the last row to grad_b[n].
+hipError_t launch_wgrad_reduce(const float* partial, int splits, int rows, int Np, int cin, int cin_real, int cout,
+                               float* grad_w, float* grad_b, hipStream_t s);
 
 // gpre[p][c] = bf16(g[p * ld + c]), c < C, zero for C <= c < Cp.
 hipError_t launch_grad_prep(long long P, int C, int Cp, const float* g, int ld, bf16_t* gpre, hipStream_t s);
@@ -118,11 +120,24 @@ inline WeightTiles weight_tiles_fwd(int taps, int cin, int np) { return {(np + 3
 inline WeightTiles weight_tiles_grad(int taps, int cin, int np, int tap_pad) {
   return {(cin + 31) / 32, tap_pad ? taps * ((np + 31) / 32) : (taps * np + 31) / 32};
 }
-// Both copies of a layer's master weights w[t][c][o] (taps x cin x np): w16 for
-// the forward convolution, wt16 for the input gradient (conv3 flips the taps,
-// t' = 8 - t; down3 and 1x1 keep them).
-hipError_t launch_cast_weights(const float* w, int taps, int cin, int np, int flip, int tap_pad, bf16_t* w16,
-                               bf16_t* wt16, hipStream_t s);
+// Both copies of every layer's master weights w[t][c][o] (taps x cin_real x
+// cout, zeros up to cin and np): w16 for the forward convolution, wt16 for the
+// input gradient (conv3 flips the taps, t' = 8 - t; down3 and 1x1 keep them).
+constexpr int kCastLayers = 24;
+struct CastLayer {
+  long long w_off, f_off, t_off;  // elements into w, w16, wt16
+  int taps, cin, cin_real, cout, np, flip, tap_pad;
+  int steps_f, steps_t;           // set by the launcher, as the following
+  long long n_f, n_t;
+  unsigned first;                 // first block of the layer
+};
+struct CastArgs {
+  const float* w;
+  bf16_t *w16, *wt16;
+  int layers;
+  CastLayer layer[kCastLayers];
+};
+hipError_t launch_cast_weights(const CastArgs& a, hipStream_t s);
 hipError_t launch_adam(long long n, float* w, const float* g, float* m, float* v, float lr, float b1, float b2,
                        float eps, float c1, float c2, hipStream_t s);
 hipError_t launch_fill_f32(float* p, long long n, float v, hipStream_t s);

@@ -668,8 +668,8 @@ __global__ __launch_bounds__(256, 2) void wgrad_kernel(WgradArgs a) {
 
 // Sum of the splits: 64 elements a block, a quarter of the splits per wave
 // (loads of eight splits in flight), the quarters added in order.
-__global__ __launch_bounds__(256) void wgrad_reduce_kernel(const float* partial, int splits, int rows, int Np,
-                                                           float* gw, float* gb) {
+__global__ __launch_bounds__(256) void wgrad_reduce_kernel(const float* partial, int splits, int rows, int Np, int cin,
+                                                           int cin_real, int cout, float* gw, float* gb) {
   __shared__ float red[4][64];
   const long long n_el = (long long)rows * Np;
   const int lane = threadIdx.x & 63, q = threadIdx.x >> 6;
@@ -692,9 +692,12 @@ __global__ __launch_bounds__(256) void wgrad_reduce_kernel(const float* partial,
   __syncthreads();
   if (q == 0 && e < n_el) {
     s = ((red[0][lane] + red[1][lane]) + red[2][lane]) + red[3][lane];
-    const long long r = e / Np;
-    if (r < rows - 1) gw[e] = s;
-    else gb[e - r * Np] = s;
+    const int r = (int)(e / Np), n = (int)(e - (long long)r * Np);
+    if (n < cout) {
+      const int t = r / cin, c = r - t * cin;
+      if (r == rows - 1) gb[n] = s;
+      else if (c < cin_real) gw[((long long)t * cin_real + c) * cout + n] = s;
+    }
   }
 }
 
@@ -852,29 +855,39 @@ __global__ void make_field_kernel(int B, int N, const float* pred, int transpose
 // reduction index 32 s + 8 (l / 16) + e; zeros beyond the operand's rows and
 // reduction.  Forward: row o, k = t cin + c.  Input gradient: row c,
 // k = t' np + o, each tap's np padded to whole steps for a stride-3 layer
-// (whose launches take one tap each).
-__global__ void cast_weights_kernel(const float* w, int taps, int cin, int np, int flip, int tap_pad, int steps_f,
-                                    long long n_f, int steps_t, long long n_t, bf16_t* w16, bf16_t* wt16) {
-  for (long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x; e < n_f + n_t;
-       e += (long long)gridDim.x * blockDim.x) {
-    const bool fwd = e < n_f;
-    const long long q = fwd ? e : e - n_f;
+// (whose launches take one tap each).  A thread writes the eight elements of a
+// lane; one launch covers all layers (a launch each: 21 of 4.5 us).
+constexpr int kCastUnits = 512;  // lanes' parts per block
+__global__ __launch_bounds__(256) void cast_weights_kernel(CastArgs a) {
+  int li_ = 0;
+  while (li_ + 1 < a.layers && blockIdx.x >= a.layer[li_ + 1].first) ++li_;
+  const CastLayer& L = a.layer[li_];
+  const float* w = a.w + L.w_off;
+  const long long base = (long long)(blockIdx.x - L.first) * kCastUnits, units = (L.n_f + L.n_t) / 8;
+  for (int u = threadIdx.x; u < kCastUnits && base + u < units; u += 256) {
+    const long long e = (base + u) * 8;
+    const bool fwd = e < L.n_f;
+    const long long q = fwd ? e : e - L.n_f;
     const int l = (int)(q >> 3) & 63, li = l & 15;
-    const int ts = (int)(q >> 9), S = fwd ? steps_f : steps_t;
+    const int ts = (int)(q >> 9), S = fwd ? L.steps_f : L.steps_t;
     const int t2 = ts / S, s = ts - t2 * S;
     const int row = 32 * (t2 >> 1) + 8 * (li >> 2) + 4 * (t2 & 1) + (li & 3);
-    const int k = 32 * s + 8 * (l >> 4) + (int)(q & 7);
-    float v = 0.f;
-    if (fwd) {
-      if (row < np && k < taps * cin) v = w[(long long)k * np + row];
-      w16[q] = f2bf(v);
-    } else {
-      const int per = tap_pad ? (np + 31) / 32 * 32 : np;
-      const int tt = k / per, o = k - tt * per;
-      const int t = flip ? taps - 1 - tt : tt;
-      if (row < cin && tt < taps && o < np) v = w[((long long)t * cin + row) * np + o];
-      wt16[q] = f2bf(v);
+    const int k0 = 32 * s + 8 * (l >> 4);
+    // forward: k = t cin + c; input gradient: k = t' per + o
+    const int per = fwd ? L.cin : (L.tap_pad ? (L.np + 31) / 32 * 32 : L.np);
+    uint32_t h[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const int k = k0 + j;
+      const int tt = k / per, x = k - tt * per;
+      const int t = !fwd && L.flip ? L.taps - 1 - tt : tt;
+      const int c = fwd ? x : row, o = fwd ? row : x;
+      float v = 0.f;
+      if (tt < L.taps && c < L.cin_real && o < L.cout) v = w[((long long)t * L.cin_real + c) * L.cout + o];
+      h[j] = f2bf(v);
     }
+    *reinterpret_cast<uint4*>((fwd ? a.w16 + L.f_off : a.wt16 + L.t_off) + q) =
+        uint4{h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16)};
   }
 }
 
@@ -974,9 +987,10 @@ hipError_t launch_wgrad(const WgradArgs& a, int splits, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_wgrad_reduce(const float* partial, int splits, int rows, int Np, float* gw, float* gb, hipStream_t s) {
+hipError_t launch_wgrad_reduce(const float* partial, int splits, int rows, int Np, int cin, int cin_real, int cout,
+                               float* gw, float* gb, hipStream_t s) {
   hipLaunchKernelGGL(wgrad_reduce_kernel, dim3((unsigned)(((long long)rows * Np + 63) / 64)), dim3(256), 0, s, partial,
-                     splits, rows, Np, gw, gb);
+                     splits, rows, Np, cin, cin_real, cout, gw, gb);
   return hipGetLastError();
 }
 
@@ -1019,11 +1033,20 @@ hipError_t launch_make_field(int B, int N, const float* pred, int transpose, int
   return hipGetLastError();
 }
 
-hipError_t launch_cast_weights(const float* w, int taps, int cin, int np, int flip, int tap_pad, bf16_t* w16,
-                               bf16_t* wt16, hipStream_t s) {
-  const WeightTiles f = weight_tiles_fwd(taps, cin, np), t = weight_tiles_grad(taps, cin, np, tap_pad);
-  hipLaunchKernelGGL(cast_weights_kernel, dim3(grid_for(f.elements() + t.elements())), dim3(256), 0, s, w, taps, cin,
-                     np, flip, tap_pad, f.steps, f.elements(), t.steps, t.elements(), w16, wt16);
+hipError_t launch_cast_weights(const CastArgs& in, hipStream_t s) {
+  CastArgs a = in;
+  unsigned blocks = 0;
+  for (int i = 0; i < a.layers; ++i) {
+    CastLayer& L = a.layer[i];
+    const WeightTiles f = weight_tiles_fwd(L.taps, L.cin, L.np), t = weight_tiles_grad(L.taps, L.cin, L.np, L.tap_pad);
+    L.steps_f = f.steps;
+    L.steps_t = t.steps;
+    L.n_f = f.elements();
+    L.n_t = t.elements();
+    L.first = blocks;
+    blocks += (unsigned)(((L.n_f + L.n_t) / 8 + kCastUnits - 1) / kCastUnits);
+  }
+  hipLaunchKernelGGL(cast_weights_kernel, dim3(blocks), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 

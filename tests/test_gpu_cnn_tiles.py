@@ -5,9 +5,11 @@ and the widest channel counts.  The comparison and its tolerances are those
 of test_gpu_cnn_ops (floating-point sums against the magnitudes of their
 terms)."""
 
+import numpy as np
 import pytest
 
 import test_gpu_cnn_ops as ops
+from oracle import cnn_oracle as co
 
 pytestmark = pytest.mark.gpu
 
@@ -44,3 +46,38 @@ CASES = [
 @pytest.mark.parametrize("case", CASES, ids=ops._case_id)
 def test_layer_edges(case, op):
     {"forward": ops.test_layer_forward, "dgrad": ops.test_layer_dgrad, "wgrad": ops.test_layer_wgrad}[op](case)
+
+
+@pytest.mark.parametrize("c0", [8, 24, 32])
+def test_parameters_round_trip_and_reach_the_layers(c0):
+    """set_params / get_params keep every value; the forward and the
+    input-gradient copies of the weights (one launch for all layers) are those
+    of the layer that owns them: a layer whose weights are zero but for one
+    yields that one weight."""
+    from paper_1004_1122_amd import cnn
+    net = cnn.WarmStartNet(c0, seed=3)
+    rng = np.random.default_rng(c0)
+    vec = rng.standard_normal(net.n_params).astype(np.float32)
+    net.set_params(vec)
+    np.testing.assert_array_equal(net.get_params(), vec)
+    n = 27
+    for index, (name, kind, _, _) in enumerate(co.layer_specs(c0)):
+        if kind != "conv3" or name.startswith("up") or index == 0:
+            continue
+        _, hi, ho, cin, cout = cnn.layer_geometry(index, n, c0)
+        params = {k: [np.zeros_like(w), np.zeros_like(b)] for k, (w, b) in cnn.unpack(vec, c0).items()}
+        ci, o = cin - 3, cout - 2
+        params[name][0][1, 1, ci, o] = 1.5
+        net.set_params(cnn.pack(params, c0))
+        x = torch.zeros((1, hi, hi, cin), dtype=torch.bfloat16)
+        x[0, 0, 0, ci] = 2.0
+        _, yf = net.layer_forward(index, x, n)
+        want = np.zeros((1, ho, ho, cout), np.float32)
+        want[0, 0, 0, o] = 3.0
+        np.testing.assert_array_equal(yf.cpu().numpy(), want)
+        gy = torch.zeros((1, ho, ho, cout), dtype=torch.bfloat16)
+        gy[0, 0, 0, o] = 2.0
+        gx = net.layer_dgrad(index, gy, n).cpu().numpy()
+        want = np.zeros((1, hi, hi, cin), np.float32)
+        want[0, 0, 0, ci] = 3.0
+        np.testing.assert_array_equal(gx, want)
