@@ -140,6 +140,7 @@ struct Group {
   std::vector<int> warm_has;    // batched: problem p brings one
   std::map<std::pair<int, int>, hipGraphExec_t>* graph_cache = nullptr;
   bool in_cg = false;           // the CG-loop passes are being queued (timed when enabled)
+  bool basic_step = false;      // the passes of a basic step are being queued: the inverse one tests the step before
   bool eq = false;              // the iteration loop forms the equilibrium norm (FP64)
   PassTimer* timer = nullptr;   // event timing of the CG-loop passes (null: off)
 };

@@ -602,6 +602,7 @@ hipError_t enq_inverse_from_c(Group& g, const Bufs<T>& b, const cx<T>* c_in, cx<
     a.p_io = p_io;
     a.r_in = r_in;
     a.cg_step = p_io != nullptr;
+    a.basic_step = g.basic_step ? 1 : 0;
     // the CG loop's update leaves x to this step (one read of p fewer)
     a.x_io = (a.cg_step && g.in_cg && cg_defers_x(g)) ? b.v[0] : nullptr;
     a.gate = gate;
@@ -620,6 +621,7 @@ hipError_t enq_inverse_from_c(Group& g, const Bufs<T>& b, const cx<T>* c_in, cx<
   a.p_io = p_io;
   a.r_in = r_in;
   a.cg_step = p_io != nullptr;
+  a.basic_step = g.basic_step ? 1 : 0;
   a.eq = eq;
   a.gate = gate;
   if ((e = timed_launch(g, LSHOM_PASS_AXIS0_INVERSE, [&] { return launch_col(a, stream_of(g)); })) != hipSuccess)
@@ -729,16 +731,19 @@ hipError_t enq_true_residual(Group& g, const Bufs<T>& b, const cx<T>* x, const d
 
 // One step of the basic scheme (Sec. 2.3, Eq. (18)) in the spectral
 // coordinate: x <- -(1/l0) P dL (E + u(x)), i.e. e^(m+1) = e0 - B e^(m); the
-// step x_new - x (the residual of e^(m)) is reduced for the tests.
+// step x_new - x (the residual of e^(m)) is reduced for the tests, which the
+// next step takes first (with the equilibrium sums: a launch after each step).
 hipError_t enq_ffth_iteration(Group& g, const Bufs<double>& b, int gate) {
   hipError_t e;
   cx<double>* x = b.v[0];
   g.in_cg = true;
+  g.basic_step = !g.eq;
   e = enq_apply_spec<double>(g, b, x, nullptr, nullptr, nullptr, x, x, 0.0, -1.0, 3, PART_RR0, gate,
                              g.eq ? 1 : 0);
   g.in_cg = false;
-  if (e != hipSuccess) return e;
-  return enq_finalize(g, FZ_FFTH, col0_block_count(g, b), gate, g.eq ? 1 : 0);
+  g.basic_step = false;
+  if (e != hipSuccess || !g.eq) return e;
+  return enq_finalize(g, FZ_FFTH, 0, gate, 1);
 }
 
 // r0 for x0 = E: r0 = -(1/l0) P dL E.
@@ -1314,7 +1319,7 @@ lshom_status solve_group(Group& g, const std::vector<DevState>& init, const lsho
         hipError_t e = enq_ffth_iteration(g, f64, GATE_ACTIVE);
         if (e != hipSuccess) return e;
       }
-      return hipSuccess;
+      return g.eq ? hipSuccess : enq_finalize(g, FZ_FFTH, 0, GATE_ACTIVE, 0);
     });
   } else if (!mixed) {
     s = run_blocks(g, 2 * eq_loop, K, per, adapt, [&](int n) -> hipError_t {

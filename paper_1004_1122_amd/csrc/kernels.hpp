@@ -120,7 +120,7 @@ enum FinMode : int {
   FZ_LEFF = 3,          // leff[c] = sum(AUX[3 b + c]) / |N|
   FZ_REFRESH = 4,       // mixed: rr_true = sum(AUX); new reference; done tests
   FZ_REFRESH_INIT = 5,  // mixed: as FZ_REFRESH without counting a refresh
-  FZ_FFTH = 6,          // basic scheme: norms of the step sum(RR0), sum(EQ0); count; done tests
+  FZ_FFTH = 6,          // basic scheme: norms of the step sum(RR0), sum(EQ0); done tests
   FZ_BICG_START = 7,    // BiCG: rho = sum(AUX[3b]), (r, r) = sum(AUX[3b + 1]); done tests
   FZ_BICG_ALPHA = 8,    // BiCG: alpha = rho / sum(PQ) (breakdown when zero or not finite)
   FZ_BICG_STEP = 9,     // BiCG: rho' and (r, r) of the new iterate; beta; count; done tests
@@ -228,6 +228,7 @@ struct ColArgs {
   cx<T>* p_io;           // cg_step: p = r + beta p (written back)
   const cx<T>* r_in;
   int cg_step;           // this launch is the CG direction step (decides beta, stop)
+  int basic_step;        // COL_INV_C from c_in: the basic scheme's test of its last step comes first
   int pipe;              // pipelined CG: COL_INV_C takes the scalar step (alpha, beta,
                          // stop) from (r, r), (w, r); COL_FWD_PROJ adds beta * out
   // COL_FWD_PROJ: out = coef_base * base + coef_s * [1 / l0 if s_inv_l0] * s
@@ -423,6 +424,7 @@ struct W3Args {
   cx<T>* p_io;
   const cx<T>* r_in;
   int cg_step;
+  int basic_step;       // as in ColArgs
   cx<T>* x_io;                   // CG step: applies a pending x += alpha_log p (x_pend)
   // W3_COL1
   int dir;

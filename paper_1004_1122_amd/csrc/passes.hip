@@ -539,7 +539,7 @@ __global__ __launch_bounds__(NT) void col_kernel(ColArgs<T> a) {
   static_assert(kBatch % kNV == 0, "a batch of elements covers every share");
   const bool pipe = kGen && a.pipe;
   const bool aniso = kGen && a.aniso;
-  if (!(kInv && (a.cg_step || pipe)) && gated_out_stable(st, a.gate)) return;
+  if (!(kInv && (a.cg_step || a.basic_step || pipe)) && gated_out_stable(st, a.gate)) return;
   const ProbEntry* pe = a.bt.tab ? a.bt.tab + pb : nullptr;
   Partials parts = a.parts;
   parts.base += (long long)pb * a.bt.pstride;
@@ -576,6 +576,8 @@ __global__ __launch_bounds__(NT) void col_kernel(ColArgs<T> a) {
     if (pipe) {
       if (!pipe_direction<NT, kNV>(st, parts, a.inv_n, a.gate, bx == 0)) return;
     } else if (a.cg_step && !cg_direction<NT, kNV>(st, parts, a.inv_n, &beta, a.gate, a.eq, bx == 0)) {
+      return;
+    } else if (a.basic_step && !basic_direction<NT, kNV>(st, parts, a.inv_n, a.gate, bx == 0)) {
       return;
     }
     const T tb = (T)beta;
@@ -792,6 +794,7 @@ __global__ __launch_bounds__(NT) void col_kernel(ColArgs<T> a) {
       if (a.eq && a.dot != 1) parts.region(a.eq_region)[bx] = sum[1];
     }
     if (a.dot_region == PART_RR0 && bx == 0 && tid == 0) st->nparts[0] = (int)gridDim.x;
+    if (a.dot == 3 && bx == 0 && tid == 0) st->iter_a += 1;
     if (a.dot_region == PART_PQ && bx == 0 && tid == 0) st->nparts_pq = (int)gridDim.x;
   }
   }
@@ -1267,8 +1270,9 @@ __global__ __launch_bounds__(256) void finalize_kernel(FinArgs a) {
       break;
     }
     case FZ_FFTH: {
-      // iterate m was transformed into m + 1; the step is its residual
-      const int m = st->iter_a;
+      // iterate m was transformed into m + 1 = iter_a (counted by the pass
+      // that ends the step); the step is the residual of m
+      const int m = st->iter_a - 1;
       // the step's producer set nparts[0] (a wide one had its partials folded)
       const double rr = sum_partials<NT>(parts.region(PART_RR0), st->nparts[0]) * a.inv_n;
       bool conv = rr <= st->tol2b2;
@@ -1279,7 +1283,6 @@ __global__ __launch_bounds__(256) void finalize_kernel(FinArgs a) {
       }
       if (lead) {
         st->rr_log = rr;
-        st->iter_a = m + 1;
         st->iter_u = m;
         if (!isfinite(rr)) {
           st->status = -6;

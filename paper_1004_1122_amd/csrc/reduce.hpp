@@ -279,6 +279,32 @@ __device__ bool cg_direction(DevState* st, const Partials& parts, double inv_n, 
   return !stop;
 }
 
+// The test of the basic scheme on its last step (iter_a counts the steps
+// taken, by the pass that ends one), at the start of the next: false when the
+// block must not compute it.  Identical decision in every block; the one with
+// lead_block set records it.  (Residual norm only: the equilibrium norm is
+// tested after each step.)  A launch of its own for the test took 5 of the 43
+// us of a step on 255^2.
+template <int NT, int NV = 1>
+__device__ bool basic_direction(DevState* st, const Partials& parts, double inv_n, int gate, bool lead_block) {
+  const int skip0 = gate_flags(st, gate);
+  const int m = st->iter_a;
+  double share[1][NV], v[1];
+  partial_shares<NT, NV>(parts.region(PART_RR0), m > 0 ? st->nparts[0] : 0, share[0]);
+  if (block_sums_shared<NT, 1, NV>(share, v, skip0)) return false;
+  if (m == 0) return true;
+  const double rr = v[0] * inv_n;
+  const bool bad = !isfinite(rr), conv = rr <= st->tol2b2, over = m >= st->max_iter;
+  if (lead_block && threadIdx.x == 0) {
+    st->rr_log = rr;
+    st->iter_u = m - 1;
+    if (bad) st->status = -6;
+    else if (!conv && over) st->status = -5;
+    if (bad || conv || over) st->done = 1;
+  }
+  return !(bad || conv || over);
+}
+
 // The scalar step of pipelined CG at the start of iteration k = iter_a, from
 // gamma_k = (r_k, r_k) (region k & 1) and delta_k = (w_k, r_k) (PQ), both
 // reduced by the update that formed r_k and w_k: the stop tests as in

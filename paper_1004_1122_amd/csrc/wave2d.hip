@@ -158,6 +158,8 @@ __global__ __launch_bounds__(W2<N>::NT) void w2_inv_kernel(ColArgs<T> a) {
         a.p_io[col + LPS * r] = cv[r];
       }
     }
+  } else if (a.basic_step) {
+    if (!basic_direction<NT>(st, parts, a.inv_n, a.gate, blockIdx.x == 0)) return;
   } else if (gated_out_stable(st, a.gate)) {
     return;
   }
@@ -284,6 +286,7 @@ __global__ __launch_bounds__(W2<N>::NT) void w2_fwd_kernel(ColArgs<T> a) {
       parts.region(a.dot_region)[blockIdx.x] = acc[0];
       if (a.eq && a.dot != 1) parts.region(a.eq_region)[blockIdx.x] = acc[1];
       if (a.dot_region == PART_RR0 && blockIdx.x == 0) st->nparts[0] = (int)gridDim.x;
+      if (a.dot == 3 && blockIdx.x == 0) st->iter_a += 1;
       if (a.dot_region == PART_PQ && blockIdx.x == 0) st->nparts_pq = (int)gridDim.x;
     }
   }

@@ -208,6 +208,8 @@ __global__ __launch_bounds__(w3_col_threads<N0>()) void w3_inv0_kernel(W3Args<T>
   bool go = true;
   if (a.cg_step) {
     go = cg_direction<NT>(st, parts, a.inv_nd, &beta, a.gate, 0, bx == 0);
+  } else if (a.basic_step) {
+    if (!basic_direction<NT>(st, parts, a.inv_nd, a.gate, bx == 0)) return;
   } else if (gated_out_stable(st, a.gate)) {
     return;
   }
@@ -717,6 +719,7 @@ __global__ __launch_bounds__(w3_col_threads<N0>()) void w3_fwd0_kernel(W3Args<T>
   if (a.dot) {
     store_partial<NT>(acc, parts.region(a.dot_region) + bx);
     if (a.dot_region == PART_RR0 && bx == 0 && threadIdx.x == 0) st->nparts[0] = (int)gridDim.x;
+    if (a.dot == 3 && bx == 0 && threadIdx.x == 0) st->iter_a += 1;
     if (a.dot_region == PART_PQ && bx == 0 && threadIdx.x == 0) st->nparts_pq = (int)gridDim.x;
   }
 }
