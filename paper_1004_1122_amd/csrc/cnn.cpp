@@ -206,7 +206,7 @@ Plan make_plan(const lshom_cnn* c, int B, int N, int training) {
       const Layer& L = c->layers[i];
       const long long Pout = p.P[lev_of[i]];
       const int rows = L.taps * L.cin + 1;
-      pf = std::max(pf, (size_t)wgrad_splits(Pout, rows, L.np) * rows * L.np);
+      pf = std::max(pf, (size_t)wgrad_splits(Pout) * rows * L.np);
     }
     p.partial_floats = pf;
     p.partial = f32((long long)pf);
@@ -331,9 +331,9 @@ hipError_t conv_wgrad(lshom_cnn* c, const Plan& p, const Layer& L, View in, int 
   a.taps = L.taps;
   a.rows = L.taps * L.cin + 1;
   const long long P = (long long)B * Ho * Ho;
-  const int splits = wgrad_splits(P, a.rows, L.np);
+  const int splits = wgrad_splits(P);
   long long pps = (P + splits - 1) / splits;
-  pps = (pps + 127) / 128 * 128;  // whole 32-pixel steps of the four waves
+  pps = (pps + 31) / 32 * 32;  // whole 32-pixel steps
   a.pix_per_split = pps;
   float* partial = at<float>(c, p.partial);
   a.partial = partial;

@@ -64,18 +64,12 @@ struct WgradArgs {
   float* partial;        // [splits][rows][Np]
 };
 
-// Weight-gradient tile of a block: rows of the im2col matrix and output
-// channels (half the accumulators for the 32-channel layers).
-constexpr int kWgradRows = 128;
-inline int wgrad_cols(int Np) { return Np <= 32 ? 32 : 64; }
-// Pixel splits of a layer's weight gradient: about 768 blocks (three per CU,
-// two of which fit at once), each of at least 256 pixels (two steps a wave).
-inline int wgrad_splits(long long pixels, int rows, int Np) {
-  const long long tiles = (long long)((rows + kWgradRows - 1) / kWgradRows) * ((Np + wgrad_cols(Np) - 1) / wgrad_cols(Np));
-  const long long most = (pixels + 255) / 256;
-  long long s = (768 + tiles - 1) / tiles;
-  s = s < most ? s : most;
-  return (int)(s < 256 ? s : 256);
+constexpr int kWgradRows = 32;  // rows of the im2col matrix per wave
+// Pixel splits of a layer's weight gradient; each holds a multiple of 32
+// pixels (one step of the kernel).
+inline int wgrad_splits(long long pixels) {
+  const long long s = (pixels + 8191) / 8192;
+  return (int)(s < 64 ? s : 64);
 }
 
 hipError_t launch_conv(const ConvArgs& a, hipStream_t s);

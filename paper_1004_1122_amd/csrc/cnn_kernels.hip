@@ -427,22 +427,26 @@ __global__ __launch_bounds__(256) void conv_kernel(ConvArgs a) {
 //
 // A GEMM whose reduction runs over the pixels, the slow index of both
 // operands, while a matrix-core fragment wants eight consecutive pixels of
-// one channel.  Each lane reads eight channels of eight consecutive pixels
-// (16 bytes a pixel) and transposes the 8 x 8 block in registers, one byte
-// permute per word: channel t of lane li is then row li of row tile t (tile t
-// holds the rows 8 li + t), so neither operand passes through LDS and the
-// loop has no barrier.  A wave accumulates 128 rows x NB columns; the four
-// waves of a block take every fourth 32-pixel step and add up in LDS in a
-// fixed order at the end.  Bound by the vector cache's reads of the im2col
-// rows (each input value is read once per tap).
-// 16 images of 243^2, 32 -> 32 channels: 564 -> 105 us; the 21 layers of a
-// training step: 9.0 -> 1.6 ms.
+// one channel.  Each lane reads two channels of eight consecutive pixels
+// (4 bytes a pixel) and transposes the block in registers, one byte permute
+// per word: channel t of lane li is then row li of row tile t (tile t holds
+// the rows 2 li + t), so neither operand passes through LDS and the loop has
+// no barrier.  A wave owns 32 rows x NB columns of one split and adds its
+// 32-pixel steps in order, D of them in flight: the order of every sum is that
+// of the pixels within a split and of the splits, whatever the tile.  (The
+// rounding of a weight to 16 bits can hang on the last bit of a gradient near
+// zero, through Adam's normalised step: the order stays.)  Bound by the
+// chain of a split's steps, 0.4 to 0.6 us each (1.1 us where an image row is
+// shorter than a step and every pixel finds its row).
+// 16 images of 243^2, 32 -> 32 channels: 564 -> 272 us; the 21 layers of a
+// training step: 9.0 -> 4.6 ms (1.6 ms with four times the splits and four
+// waves sharing one, which added in another order: not kept).
 template <int NB>
-__global__ __launch_bounds__(256, 2) void wgrad_kernel(WgradArgs a) {
+__global__ __launch_bounds__(64, NB == 32 ? 2 : 1) void wgrad_kernel(WgradArgs a) {
   constexpr int CB = NB / 16;   // gy channels per lane
-  constexpr int RT = 8;         // row tiles per wave
-  __shared__ float red[2][RT * CB * 4][64];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  constexpr int RT = 2;         // row tiles per wave
+  constexpr int D = NB == 32 ? 6 : 4;  // steps in flight
+  const int lane = threadIdx.x & 63;
   const int li = lane & 15, g = lane >> 4;
   const int s = blockIdx.z;
   const int W = a.Wo, H = a.Ho;
@@ -450,8 +454,8 @@ __global__ __launch_bounds__(256, 2) void wgrad_kernel(WgradArgs a) {
   const long long pb0 = (long long)s * a.pix_per_split;
   const long long pend = (pb0 + a.pix_per_split < M) ? pb0 + a.pix_per_split : M;
   const int Kf = a.taps * a.C0;
-  // the lane's eight im2col rows (one tap) and CB output channels
-  const int r = blockIdx.x * kWgradRows + 8 * li;
+  // the lane's two im2col rows (one tap) and CB output channels
+  const int r = blockIdx.x * kWgradRows + 2 * li;
   const int n = blockIdx.y * NB + CB * li;
   const bool row_in = r < Kf, ones = r == Kf, col_in = n < a.Np;
   const int tap = row_in ? r / a.C0 : 0;
@@ -488,94 +492,50 @@ __global__ __launch_bounds__(256, 2) void wgrad_kernel(WgradArgs a) {
     return (uint32_t)jj;
   };
 
-  uint32_t ra[8][4];       // [pixel][channel pair]
-  uint32_t rb[8][CB / 2];
-  auto put_a = [&](int u, const uint4& v) {
-    ra[u][0] = v.x;
-    ra[u][1] = v.y;
-    ra[u][2] = v.z;
-    ra[u][3] = v.w;
-  };
-  auto load_b = [&](int u, const bf16_t* p) {
+  uint32_t ra[D][8];           // [step][pixel]: two channels
+  uint32_t rb[D][8][CB / 2];
+  auto load_b = [&](int d, int u, const bf16_t* p) {
     if constexpr (CB == 4) {
       const uint2 y = *reinterpret_cast<const uint2*>(p);
-      rb[u][0] = y.x;
-      rb[u][1] = y.y;
+      rb[d][u][0] = y.x;
+      rb[d][u][1] = y.y;
     } else {
-      rb[u][0] = *reinterpret_cast<const uint32_t*>(p);
+      rb[d][u][0] = *reinterpret_cast<const uint32_t*>(p);
     }
   };
-  // loads of the step whose first pixel of this lane is m = (b, i, j)
-  auto fetch = [&](long long m, int b, int i, int j) {
-    const bf16_t* gp = gy + m * a.ldg;
+  // Loads of the step whose first pixel of this lane is m = (b, i, j), every
+  // pixel of it within the split.  Rows and columns beyond the operands load
+  // what the first ones do: their sums are not stored.
+  const bool small = W < 8;  // eight pixels touch more than two image rows
+  auto fetch = [&](int d, long long m, int b, int i, int j, uint32_t row0, const bf16_t* gp) {
+    uint32_t off[8];
     // steps whose eight input pixels follow each other in one row (all lanes)
-    const bool run = m + 8 <= pend && j + 8 <= W && (!c3 || (a.up == 1 && j + coff >= 0 && j + 7 + coff < W));
+    const bool run = j + 8 <= W && (!c3 || (a.up == 1 && j + coff >= 0 && j + 7 + coff < W));
     if (__all(run)) {
-      const uint4 fill = {ones ? 0x3F80u : 0u, 0u, 0u, 0u};  // 1.0 in the first row of the ones group
-      uint32_t off = (in_row(b, i) + (uint32_t)(cstep * j + coff)) * ld;
+      off[0] = (row0 + (uint32_t)(cstep * j + coff)) * ld;
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        put_a(u, fill);
-#pragma unroll
-        for (int c = 0; c < CB / 2; ++c) rb[u][c] = 0u;
-      }
-      if (row_in) {
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-          put_a(u, *reinterpret_cast<const uint4*>(in + off));
-          off += (uint32_t)cstep * ld;
-        }
-      }
-      if (col_in) {
-#pragma unroll
-        for (int u = 0; u < 8; ++u) load_b(u, gp + u * a.ldg);
-      }
-      return;
-    }
-    const bool small = W < 8;  // eight pixels touch more than two image rows
-    const bool full = m + 8 <= pend;
-    uint32_t row0 = 0, row1 = 0;
-    if (!small) {
+      for (int u = 1; u < 8; ++u) off[u] = off[u - 1] + (uint32_t)cstep * ld;
+    } else if (!small) {
       const bool wrap = i + 1 == H;
-      row0 = in_row(b, i);
-      row1 = in_row(wrap ? b + 1 : b, wrap ? 0 : i + 1);  // read only where it is a pixel of the batch
-    }
-    if (!small && __all(full)) {
-      // steps across a row's end: every pixel valid, no masks
-      const uint4 fill = {ones ? 0x3F80u : 0u, 0u, 0u, 0u};
+      const uint32_t row1 = in_row(wrap ? b + 1 : b, wrap ? 0 : i + 1);  // used only where it is a pixel of the batch
 #pragma unroll
       for (int u = 0; u < 8; ++u) {
-        put_a(u, fill);
-#pragma unroll
-        for (int c = 0; c < CB / 2; ++c) rb[u][c] = 0u;
+        const int ju = j + u;
+        const bool next = ju >= W;
+        off[u] = ((next ? row1 : row0) + in_col(next ? ju - W : ju)) * ld;
       }
-      if (row_in) {
+    } else {
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-          const int ju = j + u;
-          const bool next = ju >= W;
-          put_a(u, *reinterpret_cast<const uint4*>(in + ((next ? row1 : row0) + in_col(next ? ju - W : ju)) * ld));
-        }
-      }
-      if (col_in) {
-#pragma unroll
-        for (int u = 0; u < 8; ++u) load_b(u, gp + u * a.ldg);
-      }
-      return;
-    }
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const bool pv = m + u < pend;
-      put_a(u, uint4{(ones && pv) ? 0x3F80u : 0u, 0u, 0u, 0u});
-      if (row_in && pv) {
+      for (int u = 0; u < 8; ++u) {
         const int bu = (int)((m + u) / hw);
         const int rem = (int)((m + u) - bu * hw);
-        put_a(u, *reinterpret_cast<const uint4*>(in + (in_row(bu, rem / W) + in_col(rem - (rem / W) * W)) * ld));
+        off[u] = (in_row(bu, rem / W) + in_col(rem - (rem / W) * W)) * ld;
       }
-#pragma unroll
-      for (int c = 0; c < CB / 2; ++c) rb[u][c] = 0u;
-      if (col_in && pv) load_b(u, gp + u * a.ldg);
     }
+#pragma unroll
+    for (int u = 0; u < 8; ++u) ra[d][u] = *reinterpret_cast<const uint32_t*>(in + off[u]);
+#pragma unroll
+    for (int u = 0; u < 8; ++u) load_b(d, u, gp + u * a.ldg);
   };
 
   float4_t acc[RT][CB];
@@ -584,114 +544,129 @@ __global__ __launch_bounds__(256, 2) void wgrad_kernel(WgradArgs a) {
 #pragma unroll
     for (int nt = 0; nt < CB; ++nt) acc[t][nt] = float4_t{0.f, 0.f, 0.f, 0.f};
 
-  // 32 pixels a step, a wave every fourth step
-  constexpr int kStride = 128;
-  const int dj = kStride % W, di = kStride / W;
-  long long m = pb0 + 32 * wave + 8 * g;
+  // 32 pixels a step; (m, b, i, j) is the fetch position
+  const int dj = 32 % W, di = 32 / W;
+  long long m = pb0 + 8 * g;
   int b = (int)(m / hw);
   int i = (int)((m - b * hw) / W);
   int j = (int)(m - ((long long)b * H + i) * W);
-  const long long first = pb0 + 32 * wave;  // wave-uniform loop bound
+  uint32_t row0 = in_row(b, i);  // of the position's row
+  const bf16_t* gp = gy + m * a.ldg;
+  auto advance = [&]() {
+    m += 32;
+    gp += 32 * a.ldg;
+    j += dj;
+    i += di;
+    if (j >= W || di > 0) {
+      if (j >= W) {
+        j -= W;
+        ++i;
+      }
+      while (i >= H) {
+        i -= H;
+        ++b;
+      }
+      row0 = in_row(b, i);
+    }
+  };
   union Frag {
     uint32_t w[4];
     bf16x8_t v;
   };
-  if (first < pend) fetch(m, b, i, j);
-  for (long long pb = first; pb < pend; pb += kStride) {
-    Frag af[RT], bf[CB];
+  const bool has_ones = __any(ones);
+  Frag af[RT], bf[CB];
+  auto fragments = [&](int d) {
+    if (has_ones && ones) {
+      // 1.0 in the first row of the group
+#pragma unroll
+      for (int u = 0; u < 8; ++u) ra[d][u] = 0x3F80u;
+    }
 #pragma unroll
     for (int t = 0; t < RT; ++t)
 #pragma unroll
       for (int k = 0; k < 4; ++k)
-        af[t].w[k] = __builtin_amdgcn_perm(ra[2 * k + 1][t >> 1], ra[2 * k][t >> 1], (t & 1) ? 0x07060302u : 0x05040100u);
+        af[t].w[k] = __builtin_amdgcn_perm(ra[d][2 * k + 1], ra[d][2 * k], t ? 0x07060302u : 0x05040100u);
 #pragma unroll
     for (int nt = 0; nt < CB; ++nt)
 #pragma unroll
       for (int k = 0; k < 4; ++k)
-        bf[nt].w[k] =
-            __builtin_amdgcn_perm(rb[2 * k + 1][nt >> 1], rb[2 * k][nt >> 1], (nt & 1) ? 0x07060302u : 0x05040100u);
-    // the next step's loads run under this step's products
-    m += kStride;
-    j += dj;
-    i += di;
-    if (j >= W) {
-      j -= W;
-      ++i;
-    }
-    while (i >= H) {
-      i -= H;
-      ++b;
-    }
-    if (pb + kStride < pend) fetch(m, b, i, j);
+        bf[nt].w[k] = __builtin_amdgcn_perm(rb[d][2 * k + 1][nt >> 1], rb[d][2 * k][nt >> 1],
+                                            (nt & 1) ? 0x07060302u : 0x05040100u);
+  };
+  auto multiply = [&]() {
 #pragma unroll
     for (int t = 0; t < RT; ++t)
 #pragma unroll
       for (int nt = 0; nt < CB; ++nt)
         acc[t][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[t].v, bf[nt].v, acc[t][nt], 0, 0, 0);
+  };
+  const int steps = pend > pb0 ? (int)((pend - pb0) / 32) : 0;  // whole steps
+#pragma unroll
+  for (int d = 0; d < D; ++d) {
+    if (d < steps) {
+      fetch(d, m, b, i, j, row0, gp);
+      advance();
+    }
+  }
+  for (int s0 = 0; s0 < steps; s0 += D) {
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+      if (s0 + d >= steps) break;
+      fragments(d);
+      if (s0 + d + D < steps) {
+        fetch(d, m, b, i, j, row0, gp);
+        advance();
+      }
+      multiply();
+    }
+  }
+  if (pb0 + 32ll * steps < pend) {
+    // the last pixels of the batch: those past the end add zeros
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const bool pv = m + u < pend;
+      ra[0][u] = 0u;
+#pragma unroll
+      for (int c = 0; c < CB / 2; ++c) rb[0][u][c] = 0u;
+      if (pv) {
+        const int bu = (int)((m + u) / hw);
+        const int rem = (int)((m + u) - bu * hw);
+        ra[0][u] = *reinterpret_cast<const uint32_t*>(in + (in_row(bu, rem / W) + in_col(rem - (rem / W) * W)) * ld);
+        load_b(0, u, gy + (m + u) * a.ldg);
+      }
+    }
+    fragments(0);
+    multiply();
   }
 
-  // waves 2 and 3 onto 0 and 1, then 1 onto 0
 #pragma unroll
-  for (int half = 2; half >= 1; half >>= 1) {
-    if (wave >= half && wave < 2 * half) {
+  for (int t = 0; t < RT; ++t)
 #pragma unroll
-      for (int t = 0; t < RT; ++t)
+    for (int e = 0; e < 4; ++e) {
+      const int ro = blockIdx.x * kWgradRows + 2 * (4 * g + e) + t;
+      if (ro >= a.rows) continue;
 #pragma unroll
-        for (int nt = 0; nt < CB; ++nt)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) red[wave - half][(t * CB + nt) * 4 + e][lane] = acc[t][nt][e];
+      for (int nt = 0; nt < CB; ++nt)
+        if (n + nt < a.Np) a.partial[((long long)s * a.rows + ro) * a.Np + n + nt] = acc[t][nt][e];
     }
-    __syncthreads();
-    if (wave < half) {
-#pragma unroll
-      for (int t = 0; t < RT; ++t)
-#pragma unroll
-        for (int nt = 0; nt < CB; ++nt)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) acc[t][nt][e] += red[wave][(t * CB + nt) * 4 + e][lane];
-    }
-    __syncthreads();
-  }
-  if (wave == 0) {
-#pragma unroll
-    for (int t = 0; t < RT; ++t)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int ro = blockIdx.x * kWgradRows + 8 * (4 * g + e) + t;
-        if (ro >= a.rows) continue;
-#pragma unroll
-        for (int nt = 0; nt < CB; ++nt)
-          if (n + nt < a.Np) a.partial[((long long)s * a.rows + ro) * a.Np + n + nt] = acc[t][nt][e];
-      }
-  }
 }
 
-// Sum of the splits: 64 elements a block, a quarter of the splits per wave
-// (loads of eight splits in flight), the quarters added in order.
-__global__ __launch_bounds__(256) void wgrad_reduce_kernel(const float* partial, int splits, int rows, int Np, int cin,
-                                                           int cin_real, int cout, float* gw, float* gb) {
-  __shared__ float red[4][64];
+// Sum of the splits in order, the loads of eight in flight.
+__global__ __launch_bounds__(64) void wgrad_reduce_kernel(const float* partial, int splits, int rows, int Np, int cin,
+                                                          int cin_real, int cout, float* gw, float* gb) {
   const long long n_el = (long long)rows * Np;
-  const int lane = threadIdx.x & 63, q = threadIdx.x >> 6;
-  const long long e = (long long)blockIdx.x * 64 + lane;
-  const int per = (splits + 3) / 4;
-  const int k1 = (q + 1) * per < splits ? (q + 1) * per : splits;
-  float s = 0.f;
+  const long long e = (long long)blockIdx.x * 64 + threadIdx.x;
   if (e < n_el) {
-    int k = q * per;
-    for (; k + 8 <= k1; k += 8) {
+    float s = 0.f;
+    int k = 0;
+    for (; k + 8 <= splits; k += 8) {
       float v[8];
 #pragma unroll
       for (int u = 0; u < 8; ++u) v[u] = partial[(long long)(k + u) * n_el + e];
 #pragma unroll
       for (int u = 0; u < 8; ++u) s += v[u];
     }
-    for (; k < k1; ++k) s += partial[(long long)k * n_el + e];
-  }
-  red[q][lane] = s;
-  __syncthreads();
-  if (q == 0 && e < n_el) {
-    s = ((red[0][lane] + red[1][lane]) + red[2][lane]) + red[3][lane];
+    for (; k < splits; ++k) s += partial[(long long)k * n_el + e];
     const int r = (int)(e / Np), n = (int)(e - (long long)r * Np);
     if (n < cout) {
       const int t = r / cin, c = r - t * cin;
@@ -980,16 +955,18 @@ hipError_t launch_conv(const ConvArgs& in, hipStream_t s) {
 
 hipError_t launch_wgrad(const WgradArgs& a, int splits, hipStream_t s) {
   const unsigned rb = (unsigned)((a.rows + kWgradRows - 1) / kWgradRows);
-  const int nb = wgrad_cols(a.Np);
+  // wide tiles read the input rows half as often, where they still give every
+  // second SIMD a wave
+  const int nb = a.Np > 32 && (long long)rb * ((a.Np + 63) / 64) * splits >= 512 ? 64 : 32;
   const dim3 grid(rb, (unsigned)((a.Np + nb - 1) / nb), (unsigned)splits);
-  if (nb == 32) hipLaunchKernelGGL(wgrad_kernel<32>, grid, dim3(256), 0, s, a);
-  else hipLaunchKernelGGL(wgrad_kernel<64>, grid, dim3(256), 0, s, a);
+  if (nb == 32) hipLaunchKernelGGL(wgrad_kernel<32>, grid, dim3(64), 0, s, a);
+  else hipLaunchKernelGGL(wgrad_kernel<64>, grid, dim3(64), 0, s, a);
   return hipGetLastError();
 }
 
 hipError_t launch_wgrad_reduce(const float* partial, int splits, int rows, int Np, int cin, int cin_real, int cout,
                                float* gw, float* gb, hipStream_t s) {
-  hipLaunchKernelGGL(wgrad_reduce_kernel, dim3((unsigned)(((long long)rows * Np + 63) / 64)), dim3(256), 0, s, partial,
+  hipLaunchKernelGGL(wgrad_reduce_kernel, dim3((unsigned)(((long long)rows * Np + 63) / 64)), dim3(64), 0, s, partial,
                      splits, rows, Np, cin, cin_real, cout, gw, gb);
   return hipGetLastError();
 }
