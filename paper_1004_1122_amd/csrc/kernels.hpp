@@ -124,6 +124,7 @@ enum FinMode : int {
   FZ_BICG_START = 7,    // BiCG: rho = sum(AUX[3b]), (r, r) = sum(AUX[3b + 1]); done tests
   FZ_BICG_ALPHA = 8,    // BiCG: alpha = rho / sum(PQ) (breakdown when zero or not finite)
   FZ_BICG_STEP = 9,     // BiCG: rho' and (r, r) of the new iterate; beta; count; done tests
+  FZ_RESULT = 10,       // FZ_RR_TRUE, and leff[c] = sum(PQ[3 b + c], b < n_leff) / |N|
 };
 
 // ---------------------------------------------------------------------------
@@ -139,12 +140,14 @@ enum RowMode : int {
   ROW_FUSED = 0,   // spectrum -> real u -> dL (E + u) -> spectrum
   ROW_INV = 1,     // spectrum -> real out = add + E + u (FP64); optional <lambda out>
   ROW_FWD = 2,     // real in (FP64, or constant E) -> [dL] in -> spectrum
+  ROW_FUSED_OUT = 3,  // FP64: ROW_FUSED with the output and <lambda out> of ROW_INV on the way
+                   // (the residual and the field of a solution from one inverse transform)
 };
 enum RowFlags : int {
   ROWF_DL = 1,        // ROW_FWD: multiply the input by dL = lambda - l0
   ROWF_CONST_E = 2,   // ROW_FWD: the input is the constant field E
   ROWF_ADD = 4,       // ROW_INV: add real_add to the output
-  ROWF_LEFF = 8,      // ROW_INV: partial sums of <lambda out> into AUX
+  ROWF_LEFF = 8,      // ROW_INV: partial sums of <lambda out> into AUX (ROW_FUSED_OUT: into PQ)
   ROWF_STATE_E = 16,  // E of each problem from its device state (not the argument)
   ROWF_DL_OUT = 32,   // ROW_INV: multiply E + u by dL = L - L0 before adding real_add
 };
@@ -385,6 +388,7 @@ struct FinArgs {
   int gate;
   Batch bt;
   int eq;                // the equilibrium sums beside the (r, r) sums are present
+  long long n_leff;       // FZ_RESULT: row blocks of ROW_FUSED_OUT
 };
 
 // ---------------------------------------------------------------------------

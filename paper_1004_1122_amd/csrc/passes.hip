@@ -325,7 +325,7 @@ __global__ __launch_bounds__(NT) void row_kernel(RowArgs<T> a) {
         // the gate, the twiddles, the conductivities and (fused pass) the
         // phase bytes, requested while the first data chunk is in flight
         if (gated_out_stable(st, a.gate)) return;
-        if constexpr (MODE == ROW_FUSED) {
+        if constexpr (MODE == ROW_FUSED || MODE == ROW_FUSED_OUT) {
           const int nph = rows_here * n;
           for (int i0 = tid; i0 < nph; i0 += 8 * NT) {
             uint8_t v[8];
@@ -363,7 +363,7 @@ __global__ __launch_bounds__(NT) void row_kernel(RowArgs<T> a) {
     __syncthreads();
     fft_lds<T, +1, NT, RS>(Z, npairs, ss, a.plan, tw, tid);
 
-    if constexpr (MODE == ROW_INV) {
+    if constexpr (MODE == ROW_INV || MODE == ROW_FUSED_OUT) {
       double acc[kMaxDim][kNV];
 #pragma unroll
       for (int c = 0; c < kMaxDim; ++c)
@@ -444,12 +444,12 @@ __global__ __launch_bounds__(NT) void row_kernel(RowArgs<T> a) {
       }
       }
       if (a.flags & ROWF_LEFF) {
-        double* dst = parts.region(PART_AUX) + (long long)bx * 3;
+        double* dst = parts.region(MODE == ROW_INV ? PART_AUX : PART_PQ) + (long long)bx * 3;
         double sum[3];
         (void)block_sums_shared<NT, 3, kNV>(acc, sum, 0);
         if (tid < 3) dst[tid] = tid == 0 ? sum[0] : (tid == 1 ? sum[1] : sum[2]);
       }
-      return;
+      if constexpr (MODE == ROW_INV) return;
     }
 
     // ROW_FUSED: polarisation dL (E + u) at the nodes (Sec. 2.2, Eq. (17))
@@ -1226,7 +1226,12 @@ __global__ __launch_bounds__(256) void finalize_kernel(FinArgs a) {
       if (lead) st->dot_aux = s;
       break;
     }
+    case FZ_RESULT:
     case FZ_RR_TRUE: {
+      for (int c = 0; a.mode == FZ_RESULT && c < a.d; ++c) {
+        const double m = sum_partials<NT>(parts.region(PART_PQ) + c, (int)a.n_leff, 3) * a.inv_n;
+        if (lead) st->leff[c] = m;
+      }
       const double s = sum_partials<NT>(parts.region(PART_AUX), a.n) * a.inv_n;
       if (a.eq) (void)equilibrium_test(st, -1, s, sum_partials<NT>(parts.region(PART_EQ0), a.n), lead);
       if (lead) st->rr_true = s;
@@ -1552,6 +1557,9 @@ template <typename T, int RS>
 static void launch_row_rs(const RowArgs<T>& a, size_t lds, long long nb, int nt, hipStream_t s) {
   if (a.mode == ROW_FUSED) launch_row_m<T, RS, ROW_FUSED>(a, lds, nb, nt, s);
   else if (a.mode == ROW_INV) launch_row_m<T, RS, ROW_INV>(a, lds, nb, nt, s);
+  else if (a.mode == ROW_FUSED_OUT) {
+    if constexpr (sizeof(T) == 8) launch_row_m<T, RS, ROW_FUSED_OUT>(a, lds, nb, nt, s);
+  }
   else launch_row_m<T, RS, ROW_FWD>(a, lds, nb, nt, s);
 }
 

@@ -416,7 +416,7 @@ __global__ __launch_bounds__(W2<N>::NT) void w2_row_kernel(RowArgs<T> a) {
     fft_sync<N>();
     cx<T> z[9];
     wave_fft_lds_regs<T, N, +1>(buf, tw, ln.j, ln.act, z);
-    if constexpr (MODE == ROW_INV) {
+    if constexpr (MODE == ROW_INV || MODE == ROW_FUSED_OUT) {
       double* out = pe ? (pe->e_out ? pe->e_out + al * nvox : nullptr) : (al == 0 ? a.real_out[0] : a.real_out[1]);
       const double* add = al == 0 ? a.real_add[0] : a.real_add[1];
       double acc = 0.0;
@@ -435,7 +435,10 @@ __global__ __launch_bounds__(W2<N>::NT) void w2_row_kernel(RowArgs<T> a) {
           if (a.flags & ROWF_LEFF) acc += (double)cond[q] * val;
         }
       }
-      if (a.flags & ROWF_LEFF) store_partial<NT>(acc, parts.region(PART_AUX) + (long long)rb * 3 + al);
+      if (a.flags & ROWF_LEFF)
+        store_partial<NT>(acc, parts.region(MODE == ROW_INV ? PART_AUX : PART_PQ) + (long long)rb * 3 + al);
+    }
+    if constexpr (MODE == ROW_INV) {
       return;
     } else {
       // polarisation dL (E + u) at the nodes (Sec. 2.2, Eq. (17))
@@ -482,6 +485,9 @@ hipError_t launch_w2_row_n(const RowArgs<T>& a, hipStream_t s) {
   const dim3 grid(2u * (unsigned)row_blocks(a), (unsigned)(a.bt.nprob > 1 ? a.bt.nprob : 1));
   if (a.mode == ROW_FUSED) hipLaunchKernelGGL((w2_row_kernel<T, N, ROW_FUSED>), grid, dim3(G::NT), lds, s, a);
   else if (a.mode == ROW_INV) hipLaunchKernelGGL((w2_row_kernel<T, N, ROW_INV>), grid, dim3(G::NT), lds, s, a);
+  else if (a.mode == ROW_FUSED_OUT) {
+    if constexpr (sizeof(T) == 8) hipLaunchKernelGGL((w2_row_kernel<T, N, ROW_FUSED_OUT>), grid, dim3(G::NT), lds, s, a);
+  }
   else hipLaunchKernelGGL((w2_row_kernel<T, N, ROW_FWD>), grid, dim3(G::NT), lds, s, a);
   return hipGetLastError();
 }

@@ -558,7 +558,7 @@ __global__ __launch_bounds__(256) void w3_row_kernel(W3Args<T> a) {
     // the inverse transform stays in registers: z[r] = node j + LPS r
     cx<T> z[9];
     wave_fft_lds_regs<T, N2, +1>(buf, tw, j, lane_ok, z);
-    if constexpr (MODE == ROW_INV) {
+    if constexpr (MODE == ROW_INV || MODE == ROW_FUSED_OUT) {
       double* out = pe ? (pe->e_out ? pe->e_out + al * nvox : nullptr) : w3_pick(a.real_out, al);
       const double* add = w3_pick(a.real_add, al);
       double acc = 0.0;
@@ -580,7 +580,10 @@ __global__ __launch_bounds__(256) void w3_row_kernel(W3Args<T> a) {
           }
         }
       }
-      if (a.flags & ROWF_LEFF) store_partial<256>(acc, parts.region(PART_AUX) + (long long)rb * 3 + al);
+      if (a.flags & ROWF_LEFF)
+        store_partial<256>(acc, parts.region(MODE == ROW_INV ? PART_AUX : PART_PQ) + (long long)rb * 3 + al);
+    }
+    if constexpr (MODE == ROW_INV) {
       return;
     } else {
       // polarisation dL (E + u) at the nodes (Sec. 2.2, Eq. (17))
@@ -764,6 +767,10 @@ hipError_t launch_w3_n(int pass, const W3Args<T>& a, hipStream_t s) {
       const size_t lds = w3_row_lds<N>(elem, a.n_phases);
       if (a.mode == ROW_FUSED) hipLaunchKernelGGL((w3_row_kernel<T, N, ROW_FUSED>), dim3(nb, rows), dim3(256), lds, s, a);
       else if (a.mode == ROW_INV) hipLaunchKernelGGL((w3_row_kernel<T, N, ROW_INV>), dim3(nb, rows), dim3(256), lds, s, a);
+      else if (a.mode == ROW_FUSED_OUT) {
+        if constexpr (sizeof(T) == 8)
+          hipLaunchKernelGGL((w3_row_kernel<T, N, ROW_FUSED_OUT>), dim3(nb, rows), dim3(256), lds, s, a);
+      }
       else hipLaunchKernelGGL((w3_row_kernel<T, N, ROW_FWD>), dim3(nb, rows), dim3(256), lds, s, a);
       break;
     }
