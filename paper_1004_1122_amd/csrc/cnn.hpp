@@ -65,6 +65,7 @@ struct WgradArgs {
 };
 
 constexpr int kWgradRows = 32;  // rows of the im2col matrix per wave
+constexpr int kWgradWaves = 4;  // waves per block: row tiles of one split, which read the same pixels
 // Pixel splits of a layer's weight gradient; each holds a multiple of 32
 // pixels (one step of the kernel).
 inline int wgrad_splits(long long pixels) {

@@ -438,16 +438,18 @@ __global__ __launch_bounds__(256) void conv_kernel(ConvArgs a) {
 // zero, through Adam's normalised step: the order stays.)  Bound by the
 // chain of a split's steps, 0.4 to 0.6 us each (1.1 us where an image row is
 // shorter than a step and every pixel finds its row).
-// 16 images of 243^2, 32 -> 32 channels: 564 -> 272 us; the 21 layers of a
-// training step: 9.0 -> 4.6 ms (1.6 ms with four times the splits and four
+// 16 images of 243^2, 32 -> 32 channels: 564 -> 236 us; the 21 layers of a
+// training step: 9.0 -> 4.3 ms (1.6 ms with four times the splits and four
 // waves sharing one, which added in another order: not kept).
 template <int NB>
-__global__ __launch_bounds__(64, NB == 32 ? 2 : 1) void wgrad_kernel(WgradArgs a) {
+__global__ __launch_bounds__(64 * kWgradWaves, 1) void wgrad_kernel(WgradArgs a) {
   constexpr int CB = NB / 16;   // gy channels per lane
   constexpr int RT = 2;         // row tiles per wave
   constexpr int D = NB == 32 ? 6 : 4;  // steps in flight
   const int lane = threadIdx.x & 63;
   const int li = lane & 15, g = lane >> 4;
+  const int rbase = (int)(blockIdx.x * kWgradWaves + (threadIdx.x >> 6)) * kWgradRows;  // the wave's first row
+  if (rbase >= a.rows) return;
   const int s = blockIdx.z;
   const int W = a.Wo, H = a.Ho;
   const long long M = (long long)a.B * H * W;
@@ -455,7 +457,7 @@ __global__ __launch_bounds__(64, NB == 32 ? 2 : 1) void wgrad_kernel(WgradArgs a
   const long long pend = (pb0 + a.pix_per_split < M) ? pb0 + a.pix_per_split : M;
   const int Kf = a.taps * a.C0;
   // the lane's two im2col rows (one tap) and CB output channels
-  const int r = blockIdx.x * kWgradRows + 2 * li;
+  const int r = rbase + 2 * li;
   const int n = blockIdx.y * NB + CB * li;
   const bool row_in = r < Kf, ones = r == Kf, col_in = n < a.Np;
   const int tap = row_in ? r / a.C0 : 0;
@@ -643,7 +645,7 @@ __global__ __launch_bounds__(64, NB == 32 ? 2 : 1) void wgrad_kernel(WgradArgs a
   for (int t = 0; t < RT; ++t)
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      const int ro = blockIdx.x * kWgradRows + 2 * (4 * g + e) + t;
+      const int ro = rbase + 2 * (4 * g + e) + t;
       if (ro >= a.rows) continue;
 #pragma unroll
       for (int nt = 0; nt < CB; ++nt)
@@ -954,13 +956,13 @@ hipError_t launch_conv(const ConvArgs& in, hipStream_t s) {
 }
 
 hipError_t launch_wgrad(const WgradArgs& a, int splits, hipStream_t s) {
-  const unsigned rb = (unsigned)((a.rows + kWgradRows - 1) / kWgradRows);
+  const unsigned rb = (unsigned)((a.rows + kWgradRows * kWgradWaves - 1) / (kWgradRows * kWgradWaves));
   // wide tiles read the input rows half as often, where they still give every
   // second SIMD a wave
-  const int nb = a.Np > 32 && (long long)rb * ((a.Np + 63) / 64) * splits >= 512 ? 64 : 32;
+  const int nb = a.Np > 32 && (long long)rb * kWgradWaves * ((a.Np + 63) / 64) * splits >= 512 ? 64 : 32;
   const dim3 grid(rb, (unsigned)((a.Np + nb - 1) / nb), (unsigned)splits);
-  if (nb == 32) hipLaunchKernelGGL(wgrad_kernel<32>, grid, dim3(64), 0, s, a);
-  else hipLaunchKernelGGL(wgrad_kernel<64>, grid, dim3(64), 0, s, a);
+  if (nb == 32) hipLaunchKernelGGL(wgrad_kernel<32>, grid, dim3(64 * kWgradWaves), 0, s, a);
+  else hipLaunchKernelGGL(wgrad_kernel<64>, grid, dim3(64 * kWgradWaves), 0, s, a);
   return hipGetLastError();
 }
 
