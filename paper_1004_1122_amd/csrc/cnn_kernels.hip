@@ -1,6 +1,8 @@
 // Warm-start network kernels for gfx950: implicit-GEMM convolutions on the
 // matrix cores (bfloat16 inputs, FP32 accumulation), the weight gradient as
 // a split-K GEMM with a fixed-order reduction, and the elementwise steps.
+#include <type_traits>
+
 #include "cnn.hpp"
 
 namespace lshom {
@@ -436,12 +438,18 @@ __global__ __launch_bounds__(256) void conv_kernel(ConvArgs a) {
 // of the pixels within a split and of the splits, whatever the tile.  (The
 // rounding of a weight to 16 bits can hang on the last bit of a gradient near
 // zero, through Adam's normalised step: the order stays.)  Bound by the
-// chain of a split's steps, 0.4 to 0.6 us each (1.1 us where an image row is
+// chain of a split's steps, 0.4 us each (0.6 us where an image row is
 // shorter than a step and every pixel finds its row).
-// 16 images of 243^2, 32 -> 32 channels: 564 -> 236 us; the 21 layers of a
-// training step: 9.0 -> 4.3 ms (1.6 ms with four times the splits and four
+// 16 images of 243^2, 32 -> 32 channels: 564 -> 200 us; the 21 layers of a
+// training step: 9.0 -> 3.1 ms (1.6 ms with four times the splits and four
 // waves sharing one, which added in another order: not kept).
-template <int NB>
+//
+// KIND: the pixel map (WG_CONV3, WG_UP3, WG_PLAIN); SMALL: images of fewer
+// than eight columns, whose steps touch more than two rows.  With the map
+// known at run time only, branches per pixel and the code of every path made the
+// step up to 1.6 times as long (4.3 ms for the 21 layers).
+enum WgradKind : int { WG_CONV3 = 0, WG_UP3 = 1, WG_PLAIN = 2 };
+template <int NB, int KIND, bool SMALL>
 __global__ __launch_bounds__(64 * kWgradWaves, 1) void wgrad_kernel(WgradArgs a) {
   constexpr int CB = NB / 16;   // gy channels per lane
   constexpr int RT = 2;         // row tiles per wave
@@ -469,27 +477,28 @@ __global__ __launch_bounds__(64 * kWgradWaves, 1) void wgrad_kernel(WgradArgs a)
   const bf16_t* in = a.in0 + (long long)b0 * a.Hi * a.Wi * a.ld0 + (row_in ? r - tap * a.C0 : 0);
   const bf16_t* gy = a.gy + (col_in ? n : 0);
   const uint32_t ld = (uint32_t)a.ld0;
-  const bool c3 = a.mode == CM_CONV3;
-  const int cstep = a.mode == CM_DOWN3 ? 3 : 1;   // input columns per output column
+  constexpr bool c3 = KIND != WG_PLAIN;
+  const int cstep = !c3 && a.mode == CM_DOWN3 ? 3 : 1;   // input columns per output column
   const int coff = c3 ? tq - 1 : (a.mode == CM_DOWN3 ? tq : 0);
 
   // first input pixel (from image b0) of the input row that output row (b, i) reads at the lane's tap
+  auto third = [](uint32_t v) -> uint32_t { return (v * 43691u) >> 17; };  // v / 3 for v < 2^16
   auto in_row = [&](int b, int i) -> uint32_t {
     int ii = cstep * i + (a.taps == 9 ? tp : 0);
-    if (c3) {
+    if constexpr (c3) {
       ii -= 1;
       ii += ii < 0 ? H : 0;
       ii -= ii >= H ? H : 0;
-      if (a.up == 3) ii = (int)((uint32_t)ii / 3u);
+      if constexpr (KIND == WG_UP3) ii = (int)third((uint32_t)ii);
     }
     return (uint32_t)((b - b0) * a.Hi + ii) * (uint32_t)a.Wi;
   };
   auto in_col = [&](int j) -> uint32_t {
     int jj = cstep * j + coff;
-    if (c3) {
+    if constexpr (c3) {
       jj += jj < 0 ? W : 0;
       jj -= jj >= W ? W : 0;
-      if (a.up == 3) jj = (int)((uint32_t)jj / 3u);
+      if constexpr (KIND == WG_UP3) jj = (int)third((uint32_t)jj);
     }
     return (uint32_t)jj;
   };
@@ -508,30 +517,31 @@ __global__ __launch_bounds__(64 * kWgradWaves, 1) void wgrad_kernel(WgradArgs a)
   // Loads of the step whose first pixel of this lane is m = (b, i, j), every
   // pixel of it within the split.  Rows and columns beyond the operands load
   // what the first ones do: their sums are not stored.
-  const bool small = W < 8;  // eight pixels touch more than two image rows
   auto fetch = [&](int d, long long m, int b, int i, int j, uint32_t row0, const bf16_t* gp) {
     uint32_t off[8];
-    // steps whose eight input pixels follow each other in one row (all lanes)
-    const bool run = j + 8 <= W && (!c3 || (a.up == 1 && j + coff >= 0 && j + 7 + coff < W));
-    if (__all(run)) {
-      off[0] = (row0 + (uint32_t)(cstep * j + coff)) * ld;
-#pragma unroll
-      for (int u = 1; u < 8; ++u) off[u] = off[u - 1] + (uint32_t)cstep * ld;
-    } else if (!small) {
-      const bool wrap = i + 1 == H;
-      const uint32_t row1 = in_row(wrap ? b + 1 : b, wrap ? 0 : i + 1);  // used only where it is a pixel of the batch
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const int ju = j + u;
-        const bool next = ju >= W;
-        off[u] = ((next ? row1 : row0) + in_col(next ? ju - W : ju)) * ld;
-      }
-    } else {
+    if constexpr (SMALL) {
 #pragma unroll
       for (int u = 0; u < 8; ++u) {
         const int bu = (int)((m + u) / hw);
         const int rem = (int)((m + u) - bu * hw);
         off[u] = (in_row(bu, rem / W) + in_col(rem - (rem / W) * W)) * ld;
+      }
+    } else {
+      // steps whose eight input pixels follow each other in one row (all lanes)
+      const bool run = KIND != WG_UP3 && j + 8 <= W && (!c3 || (j + coff >= 0 && j + 7 + coff < W));
+      if (KIND != WG_UP3 && __all(run)) {
+        off[0] = (row0 + (uint32_t)(cstep * j + coff)) * ld;
+#pragma unroll
+        for (int u = 1; u < 8; ++u) off[u] = off[u - 1] + (uint32_t)cstep * ld;
+      } else {
+        const bool wrap = i + 1 == H;
+        const uint32_t row1 = in_row(wrap ? b + 1 : b, wrap ? 0 : i + 1);  // used only where it is a pixel of the batch
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          const int ju = j + u;
+          const bool next = ju >= W;
+          off[u] = ((next ? row1 : row0) + in_col(next ? ju - W : ju)) * ld;
+        }
       }
     }
 #pragma unroll
@@ -961,8 +971,18 @@ hipError_t launch_wgrad(const WgradArgs& a, int splits, hipStream_t s) {
   // second SIMD a wave
   const int nb = a.Np > 32 && (long long)rb * kWgradWaves * ((a.Np + 63) / 64) * splits >= 512 ? 64 : 32;
   const dim3 grid(rb, (unsigned)((a.Np + nb - 1) / nb), (unsigned)splits);
-  if (nb == 32) hipLaunchKernelGGL(wgrad_kernel<32>, grid, dim3(64 * kWgradWaves), 0, s, a);
-  else hipLaunchKernelGGL(wgrad_kernel<64>, grid, dim3(64 * kWgradWaves), 0, s, a);
+  const int kind = a.mode != CM_CONV3 ? WG_PLAIN : (a.up == 3 ? WG_UP3 : WG_CONV3);
+  auto launch = [&](auto NB, auto KIND) {
+    if (a.Wo < 8) hipLaunchKernelGGL((wgrad_kernel<NB(), KIND(), true>), grid, dim3(64 * kWgradWaves), 0, s, a);
+    else hipLaunchKernelGGL((wgrad_kernel<NB(), KIND(), false>), grid, dim3(64 * kWgradWaves), 0, s, a);
+  };
+  auto launch_kind = [&](auto NB) {
+    if (kind == WG_CONV3) launch(NB, std::integral_constant<int, WG_CONV3>{});
+    else if (kind == WG_UP3) launch(NB, std::integral_constant<int, WG_UP3>{});
+    else launch(NB, std::integral_constant<int, WG_PLAIN>{});
+  };
+  if (nb == 32) launch_kind(std::integral_constant<int, 32>{});
+  else launch_kind(std::integral_constant<int, 64>{});
   return hipGetLastError();
 }
 
