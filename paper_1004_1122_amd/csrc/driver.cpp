@@ -452,6 +452,7 @@ hipError_t enq_finalize(Group& g, int mode, long long n, int gate, int eq = 0, l
   f.mode = mode;
   f.n = (int)n;
   f.n_leff = n_leff;
+  f.j_from_leff = g.w3 ? 1 : 0;
   f.d = g.d;
   f.inv_n = 1.0 / (double)g.nvox;
   f.gate = gate;
@@ -554,6 +555,7 @@ hipError_t enq_forward_project(Group& g, const Bufs<T>& b, cx<T>* out, const cx<
     f.s_inv_l0 = s_inv_l0;
     f.dot = dot;
     f.dot_region = dot_region;
+    f.eq = eq;
     f.gate = gate;
     if ((e = timed_launch(g, LSHOM_PASS_AXIS0_FORWARD, [&] { return launch_w3(W3_FWD0, f, stream_of(g)); })) !=
         hipSuccess)

@@ -389,6 +389,7 @@ struct FinArgs {
   Batch bt;
   int eq;                // the equilibrium sums beside the (r, r) sums are present
   long long n_leff;       // FZ_RESULT: row blocks of ROW_FUSED_OUT
+  int j_from_leff;        // FZ_RESULT with eq: the producer left no transform at k = 0 in jx
 };
 
 // ---------------------------------------------------------------------------
@@ -451,6 +452,7 @@ struct W3Args {
   int s_inv_l0;
   double l0d;
   int dot, dot_region;
+  int eq;                        // FP64, dot 2: the equilibrium sum too, into EQ0
   DevState* st;
   Partials parts;
   int gate;

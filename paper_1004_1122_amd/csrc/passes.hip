@@ -1230,7 +1230,12 @@ __global__ __launch_bounds__(256) void finalize_kernel(FinArgs a) {
     case FZ_RR_TRUE: {
       for (int c = 0; a.mode == FZ_RESULT && c < a.d; ++c) {
         const double m = sum_partials<NT>(parts.region(PART_PQ) + c, (int)a.n_leff, 3) * a.inv_n;
-        if (lead) st->leff[c] = m;
+        if (lead) {
+          st->leff[c] = m;
+          // j_hat(0) = |N| <lambda e>: the wave passes carry the components
+          // multiplied by xi, which is 0 there
+          if (a.eq && a.j_from_leff) st->jx[c] = st->nvox * (m - st->l0E[c]);
+        }
       }
       const double s = sum_partials<NT>(parts.region(PART_AUX), a.n) * a.inv_n;
       if (a.eq) (void)equilibrium_test(st, -1, s, sum_partials<NT>(parts.region(PART_EQ0), a.n), lead);

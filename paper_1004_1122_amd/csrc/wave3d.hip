@@ -634,9 +634,10 @@ __global__ __launch_bounds__(256) void w3_row_kernel(W3Args<T> a) {
 }
 
 // ---------------------------------------------------------------------------
-// Axis-0 forward + projection: Hl -> V
+// Axis-0 forward + projection: Hl -> V.  EQ: with dot 2 also the equilibrium
+// sum of |xi|^2 |out|^2 (the residual of a returned field).
 // ---------------------------------------------------------------------------
-template <typename T, int N0>
+template <typename T, int N0, bool EQ = false>
 __global__ __launch_bounds__(w3_col_threads<N0>()) void w3_fwd0_kernel(W3Args<T> a) {
   constexpr int NT = w3_col_threads<N0>();
   constexpr int LPS = WaveGeom<N0>::LPS, CPW = w3_cpw<N0>();
@@ -695,7 +696,7 @@ __global__ __launch_bounds__(w3_col_threads<N0>()) void w3_fwd0_kernel(W3Args<T>
   }
   const T cs = a.coef_s * (a.s_inv_l0 ? (T)(1.0 / (pe ? pe->l0 : a.l0d)) : T(1));
   const double wgt = w3_weight(c, a.h);
-  double acc = 0.0;
+  double acc = 0.0, acc_eq = 0.0;
   if (act) {
     cx<T> bv[9];
 #pragma unroll
@@ -712,6 +713,11 @@ __global__ __launch_bounds__(w3_col_threads<N0>()) void w3_fwd0_kernel(W3Args<T>
         acc += wgt * ((double)bv[r].re * (double)val.re + (double)bv[r].im * (double)val.im);
       } else if (a.dot == 2) {
         acc += wgt * ((double)val.re * (double)val.re + (double)val.im * (double)val.im);
+        if constexpr (EQ) {
+          const double x0 = (double)w3_freq(j + LPS * r, N0) * a.cinv[0];
+          const double k2 = x0 * x0 + (double)x1 * (double)x1 + (double)x2 * (double)x2;
+          acc_eq += wgt * k2 * ((double)val.re * (double)val.re + (double)val.im * (double)val.im);
+        }
       } else if (a.dot == 3) {
         // the step |out - base|^2 of the basic scheme
         const double dr = (double)val.re - (double)bv[r].re, di = (double)val.im - (double)bv[r].im;
@@ -721,6 +727,7 @@ __global__ __launch_bounds__(w3_col_threads<N0>()) void w3_fwd0_kernel(W3Args<T>
   }
   if (a.dot) {
     store_partial<NT>(acc, parts.region(a.dot_region) + bx);
+    if constexpr (EQ) store_partial<NT>(acc_eq, parts.region(PART_EQ0) + bx);
     if (a.dot_region == PART_RR0 && bx == 0 && threadIdx.x == 0) st->nparts[0] = (int)gridDim.x;
     if (a.dot == 3 && bx == 0 && threadIdx.x == 0) st->iter_a += 1;
     if (a.dot_region == PART_PQ && bx == 0 && threadIdx.x == 0) st->nparts_pq = (int)gridDim.x;
@@ -775,6 +782,16 @@ hipError_t launch_w3_n(int pass, const W3Args<T>& a, hipStream_t s) {
       break;
     }
     default:
+      if (a.eq) {
+        if constexpr (sizeof(T) == 8) {
+          if (a.dot == 2) {
+            hipLaunchKernelGGL((w3_fwd0_kernel<T, N, true>), dim3((unsigned)(a.N1 * a.G), rows),
+                               dim3(w3_col_threads<N>()), w3_col_lds<N>(elem), s, a);
+            break;
+          }
+        }
+        return hipErrorInvalidValue;
+      }
       hipLaunchKernelGGL((w3_fwd0_kernel<T, N>), dim3((unsigned)(a.N1 * a.G), rows), dim3(w3_col_threads<N>()),
                          w3_col_lds<N>(elem), s, a);
       break;
