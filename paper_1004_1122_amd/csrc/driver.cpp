@@ -677,15 +677,20 @@ hipError_t enq_cg_iteration(Group& g, const Bufs<T>& b, int gate) {
 }
 
 // The iteration loop of a solve runs in one block per problem (resident2d.hip).
+// FP64 only: a mixed solve of a small image whose iterations outnumber its
+// unknowns converges or stalls by the rounding of its FP32 steps, and in one
+// block it rounds otherwise.  Of 16 solves of 27^2 images at contrast 1e4 to
+// 1e-9, none stalled on the passes and one in one block (9^2 at 1e3: one and
+// five; 63 x 70 at 1e5: none and one); with other inputs it is the other way.
+// So mixed solves stay on the passes and converge where they always did (in
+// FP64 such an image takes less time: 63^2 0.53 ms, mixed in one block 0.70).
 bool use_resident(const Group& g, int precision) {
-  return g.d == 2 && !g.eq && !g.tensor && !g.aniso && !g.timer &&
-         resident_fits(g.N, precision == LSHOM_PRECISION_FP64 ? (int)sizeof(cx<double>) : (int)sizeof(cx<float>),
-                       lds_limit_of(g));
+  return precision == LSHOM_PRECISION_FP64 && g.d == 2 && !g.eq && !g.tensor && !g.aniso && !g.timer &&
+         resident_fits(g.N, lds_limit_of(g));
 }
 
-template <typename T>
-hipError_t enq_resident(Group& g, const Bufs<T>& b, int iters, bool basic, int gate) {
-  ResidentArgs<T> a{};
+hipError_t enq_resident(Group& g, const Bufs<double>& b, int iters, bool basic, int gate) {
+  ResidentArgs a{};
   a.N0 = (int)g.N[0];
   a.N1 = (int)g.N[1];
   a.h = g.h;
@@ -699,8 +704,7 @@ hipError_t enq_resident(Group& g, const Bufs<T>& b, int iters, bool basic, int g
   a.cond = b.cond;
   a.n_phases = g.n_phases;
   a.l0 = g.l0;
-  a.inv_n = (T)(1.0 / (double)g.nvox);
-  a.inv_nd = 1.0 / (double)g.nvox;
+  a.inv_n = 1.0 / (double)g.nvox;
   a.x = b.v[0];
   a.r = b.v[1];
   a.p = b.v[2];
@@ -1312,7 +1316,6 @@ lshom_status solve_group(Group& g, const std::vector<DevState>& init, const lsho
   lshom_status s;
   // the blocks take the buffers (and launch shapes) current when they are
   // queued: the tail of a batch may switch schedules
-  const bool resident = use_resident(g, o.precision);
   const auto first_iterations = [&]() -> hipError_t {
     for (int k = 0; k < kFirstIterations; ++k) {
       const hipError_t e = mixed ? enq_cg_iteration<float>(g, get_bufs<float>(g), GATE_NO_REFRESH)
@@ -1321,18 +1324,10 @@ lshom_status solve_group(Group& g, const std::vector<DevState>& init, const lsho
     }
     return hipSuccess;
   };
-  if (resident && !mixed) {
+  if (use_resident(g, o.precision)) {
     // one launch until every problem has stopped, nothing to capture
     s = run_blocks(g, 0, 0, kResidentIters, false, [&](int n) -> hipError_t {
-      return enq_resident<double>(g, get_bufs<double>(g), n, ffth, GATE_ACTIVE);
-    });
-  } else if (resident) {
-    // the FP32 iterations to the next refresh, then the refresh
-    s = run_blocks(g, 7, K, kResidentIters, false, [&](int n) -> hipError_t {
-      const Bufs<double> f64 = get_bufs<double>(g);
-      const Bufs<float> f32 = get_bufs<float>(g);
-      hipError_t e = enq_resident<float>(g, f32, n, false, GATE_NO_REFRESH);
-      return e != hipSuccess ? e : enq_mix_refresh(g, f64, f32, E, GATE_REFRESH);
+      return enq_resident(g, get_bufs<double>(g), n, ffth, GATE_ACTIVE);
     });
   } else if (ffth) {
     s = run_blocks(g, 3 + eq_loop, K, per, adapt, [&](int n) -> hipError_t {

@@ -474,7 +474,8 @@ __host__ __device__ inline long long w3_entries(long long N0, long long N1, long
 // axis by launch_row and launch_col.  27 nodes stay with the block passes: a
 // launch is pure latency there (10 us either way), and mixed solves of 27^2
 // images at contrasts of 1e4 and more, whose iterations outnumber the
-// unknowns, converge or stall by their rounding.
+// unknowns, converge or stall by their rounding.  (FP64 solves of images that
+// small run in one block instead, mixed ones do not for the same reason.)
 // ---------------------------------------------------------------------------
 __host__ __device__ constexpr bool w2_length(long long n) { return n == 81 || n == 243 || n == 729; }
 // scalar phases; every row mode
@@ -489,24 +490,22 @@ template <typename T> hipError_t launch_w2_row(const RowArgs<T>& a, hipStream_t 
 template <typename T> hipError_t launch_w2_col(const ColArgs<T>& a, hipStream_t s);
 
 // ---------------------------------------------------------------------------
-// Whole iterations of a small 2-D image in one block (resident2d.hip)
+// Whole FP64 iterations of a small 2-D image in one block (resident2d.hip)
 // ---------------------------------------------------------------------------
-template <typename T>
 struct ResidentArgs {
   int N0, N1, h;
   int iters;                     // iterations of this launch, at most
   FftPlan plan[2];
-  const cx<T>* tw[2];
+  const cx<double>* tw[2];
   double cinv[2];                // 1 / cell side lengths
   const uint8_t* phase;          // single problem (batched: the problem table)
-  const T* cond;
+  const double* cond;
   int n_phases;
   double l0;
-  T inv_n;
-  double inv_nd;
-  cx<T>* x;
-  cx<T>* r;
-  cx<T>* p;
+  double inv_n;
+  cx<double>* x;
+  cx<double>* r;
+  cx<double>* p;
   DevState* st;
   Partials parts;
   int gate;
@@ -515,12 +514,12 @@ struct ResidentArgs {
   int ss0, ss1;                  // LDS strides of column and row sequences
 };
 // Grids the kernel takes (scalar phases and an isotropic reference, which the
-// caller checks), and its LDS bytes.
-bool resident_fits(const int64_t* N, int elem_bytes, size_t lds_limit);
+// caller checks).
+bool resident_fits(const int64_t* N, size_t lds_limit);
 // CG iterations (direction test first, as the passes take them) until the
-// problem stops, asks for a refresh (mixed) or iters are done; basic: steps of
-// the basic scheme with its test.
-template <typename T> hipError_t launch_resident(const ResidentArgs<T>& a, bool basic, hipStream_t s);
+// problem stops or iters are done; basic: steps of the basic scheme with its
+// test.
+hipError_t launch_resident(const ResidentArgs& a, bool basic, hipStream_t s);
 
 // Host launchers (passes.hip).
 template <typename T> hipError_t launch_row(const RowArgs<T>& a, hipStream_t s);
