@@ -1104,20 +1104,21 @@ lshom_status lshom_set_schedule(lshom_ctx* c, const lshom_schedule* in) {
     return fail(c, LSHOM_ERR_UNSUPPORTED, "grid too long for one LDS-resident FFT batch");
   if (!schedule_fits(probe, s, in->precision))
     return fail(c, LSHOM_ERR_INVALID_ARG, "schedule exceeds the FFT batch or LDS limits");
+  // batched launches captured so far hold the schedules of before, whether or
+  // not the context has a problem of its own
+  DeviceGuard dg(c->device);
+  drop_batch_graphs(c);
   if (s.tail_rows > 0) {
     // a tail schedule serves batched launches only (kept under precision + 2)
     c->schedules[SchedKey(in->d, probe.N[0], probe.N[1], probe.N[2], in->precision + 2)] = s;
-    drop_batch_graphs(c);
     c->err.clear();
     return LSHOM_OK;
   }
   c->schedules[SchedKey(in->d, probe.N[0], probe.N[1], probe.N[2], in->precision)] = s;
   if (c->have_problem && c->g.d == in->d && c->g.N[0] == probe.N[0] && c->g.N[1] == probe.N[1] &&
       c->g.N[2] == probe.N[2] && schedule_fits(c->g, s, in->precision)) {
-    DeviceGuard dg(c->device);
     (void)hipStreamSynchronize(c->stream);
     drop_graphs(c->graphs);
-    drop_batch_graphs(c);
     apply_schedule(c->g, s, in->precision);
   }
   c->err.clear();
