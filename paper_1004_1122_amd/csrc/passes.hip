@@ -1590,6 +1590,7 @@ static void launch_col_rs(const ColArgs<T>& a, size_t lds, long long nb, int nt,
 
 template <typename T>
 hipError_t launch_row(const RowArgs<T>& a, hipStream_t s) {
+  if (sizeof(T) == 4 && a.mode == ROW_FUSED_OUT) return hipErrorInvalidValue;  // FP64 only
   if (w2_row(a)) return launch_w2_row(a, s);
   const int comps = a.split ? 1 : a.d;
   const size_t lds = row_lds_bytes(a.n, a.rows_per_block, comps, (int)sizeof(cx<T>), a.n_phases, nullptr);

@@ -506,6 +506,7 @@ hipError_t launch_w2_col_n(const ColArgs<T>& a, hipStream_t s) {
 
 template <typename T>
 hipError_t launch_w2_row(const RowArgs<T>& a, hipStream_t s) {
+  if (sizeof(T) == 4 && a.mode == ROW_FUSED_OUT) return hipErrorInvalidValue;  // FP64 only
   switch (a.n) {
     case 729: return launch_w2_row_n<T, 729>(a, s);
     case 243: return launch_w2_row_n<T, 243>(a, s);

@@ -819,6 +819,7 @@ long long w3_blocks(int pass, int N0, int N1, int N2) {
 
 template <typename T>
 hipError_t launch_w3(int pass, const W3Args<T>& a, hipStream_t s) {
+  if (sizeof(T) == 4 && pass == W3_ROW && a.mode == ROW_FUSED_OUT) return hipErrorInvalidValue;  // FP64 only
   // the transformed axis decides the kernel
   const int n = pass == W3_COL1 ? a.N1 : (pass == W3_ROW ? a.N2 : a.N0);
   if (n == 243) return launch_w3_n<T, 243>(pass, a, s);
