@@ -116,25 +116,28 @@ void fill_info(const DevState& hs, double l0, const lshom_solve_opts& o, int war
 }
 
 // Pinned host memory for the states of `states` problems, twice (the states
-// after a block and the initial ones; grown, never shrunk; none if the allocation fails: the states are then copied back).
-// Captured launches hold its address.
-void ensure_pinned(lshom_ctx* c, size_t states) {
-  if (c->pinned_states >= states) return;
+// after a block and the initial ones); grown, never shrunk.  Returns whether it
+// holds that many: where the allocation fails (a capture in progress on the
+// calling thread forbids it) what there was stays, and the states of a solve
+// that does not fit are copied back.  Captured launches hold its address, and
+// like every set-up it keeps clear of other contexts' captures.
+bool ensure_pinned(lshom_ctx* c, size_t states) {
+  if (c->pinned_states >= states) return true;
+  std::lock_guard<std::mutex> lock(setup_mutex());
+  void* p = nullptr;
+  if (hipHostMalloc(&p, 2 * states * sizeof(DevState), hipHostMallocDefault) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
   (void)hipStreamSynchronize(c->stream);
   drop_graphs(c->graphs);
   drop_batch_graphs(c);
   if (c->pinned) (void)hipHostFree(c->pinned);
-  c->pinned = nullptr;
-  c->pinned_states = 0;
-  void* p = nullptr;
-  if (hipHostMalloc(&p, 2 * states * sizeof(DevState), hipHostMallocDefault) == hipSuccess) {
-    c->pinned = static_cast<DevState*>(p);
-    c->pinned_states = states;
-  } else {
-    (void)hipGetLastError();
-  }
+  c->pinned = static_cast<DevState*>(p);
+  c->pinned_states = states;
   c->g.pinned = c->pinned;
-  c->g.pinned_initial = c->pinned ? c->pinned + c->pinned_states : nullptr;
+  c->g.pinned_initial = c->pinned + c->pinned_states;
+  return true;
 }
 
 hipError_t order_after_user(lshom_ctx* c) {
@@ -306,7 +309,7 @@ lshom_status lshom_create(lshom_ctx** out, int device, void* hip_stream) {
     delete c;
     return LSHOM_ERR_HIP;
   }
-  ensure_pinned(c, 64);
+  (void)ensure_pinned(c, 64);
   *out = c;
   return LSHOM_OK;
 }
@@ -319,7 +322,10 @@ void lshom_destroy(lshom_ctx* c) {
   drop_batch_graphs(c);
   for (hipEvent_t ev : c->timer.pool) (void)hipEventDestroy(ev);
   if (c->ev) (void)hipEventDestroy(c->ev);
-  if (c->pinned) (void)hipHostFree(c->pinned);
+  if (c->pinned) {
+    std::lock_guard<std::mutex> lock(setup_mutex());
+    (void)hipHostFree(c->pinned);
+  }
   for (hipStream_t st : c->group_streams) (void)hipStreamDestroy(st);
   if (c->stream) (void)hipStreamDestroy(c->stream);
   delete c;
@@ -973,6 +979,9 @@ lshom_status lshom_batch_workspace_size(lshom_ctx* c, int32_t n, const lshom_pro
   BatchPlan bp;
   lshom_status s = plan_batch(c, n, probs, precision, &bp);
   if (s != LSHOM_OK) return s;
+  // reserved with the workspace, so that the solve itself allocates nothing
+  DeviceGuard dg(c->device);
+  (void)ensure_pinned(c, (size_t)n);
   *bytes = bp.total;
   return LSHOM_OK;
 }
@@ -1008,12 +1017,12 @@ lshom_status lshom_solve_batched(lshom_ctx* c, int32_t n, const lshom_problem* p
   std::vector<std::vector<ProbEntry>> tabs(ng);
   std::vector<std::vector<DevState>> inits(ng);
   if (c->batch_graphs.size() + ng > 64) drop_batch_graphs(c);
-  ensure_pinned(c, (size_t)n);
+  const bool pinned = ensure_pinned(c, (size_t)n);
   size_t pinned_at = 0;
   for (size_t gi = 0; gi < ng; ++gi) {
     Group& g = bp.groups[gi];
-    g.pinned = c->pinned ? c->pinned + pinned_at : nullptr;
-    g.pinned_initial = c->pinned ? g.pinned + c->pinned_states : nullptr;
+    g.pinned = pinned ? c->pinned + pinned_at : nullptr;
+    g.pinned_initial = pinned ? g.pinned + c->pinned_states : nullptr;
     pinned_at += (size_t)g.nprob;
     if ((s = prepare_batch_group(c, bp, gi, probs, ws_dev, o, &tabs[gi], &inits[gi])) != LSHOM_OK) return s;
     // the captured launches carry the group's wave-vector scale 1 / Y (cell
