@@ -684,10 +684,10 @@ hipError_t enq_cg_iteration(Group& g, const Bufs<T>& b, int gate) {
 // five; 63 x 70 at 1e5: none and one); with other inputs it is the other way.
 // So mixed solves stay on the passes and converge where they always did (in
 // FP64 such an image takes less time: 63^2 0.53 ms, mixed in one block 0.70).
-bool use_resident(const Group& g, int precision) {
-  return precision == LSHOM_PRECISION_FP64 && g.d == 2 && !g.eq && !g.tensor && !g.aniso && !g.timer &&
-         resident_fits(g.N, lds_limit_of(g));
+bool resident_grid(const Group& g, int precision) {
+  return precision == LSHOM_PRECISION_FP64 && g.d == 2 && !g.tensor && !g.aniso && resident_fits(g.N, lds_limit_of(g));
 }
+bool use_resident(const Group& g, int precision) { return resident_grid(g, precision) && !g.eq && !g.timer; }
 
 hipError_t enq_resident(Group& g, const Bufs<double>& b, int iters, bool basic, int gate) {
   ResidentArgs a{};
@@ -1700,6 +1700,9 @@ lshom_status time_passes(Group& g, int precision, int reps, double* ms_out, doub
 // ---------------------------------------------------------------------------
 // Autotuner: each pass kind is tuned on its own (its radix order and launch
 // shape change only its own kernels), timing real launches on the group.
+// Passes whose launches no schedule changes (wave passes) and grids whose plain
+// solves run no passes (one block per image) keep the schedule they have: their
+// candidates would differ by noise only.
 // ---------------------------------------------------------------------------
 
 namespace {
@@ -1747,6 +1750,16 @@ std::vector<FftPlan> plan_candidates(int n) {
   return out;
 }
 
+// Whether CG solves of the group launch the row pass and the axis-0 passes as
+// the schedule says.
+template <typename T>
+void scheduled_passes(Group& g, int precision, bool* row, bool* col) {
+  const Bufs<T> b = get_bufs<T>(g);
+  const bool passes = !(g.w3ok && !g.aniso && !g.tensor) && !resident_grid(g, precision);
+  *row = passes && !w2_row(row_args(g, b));
+  *col = passes && !w2_col(col0_args(g, b));
+}
+
 template <typename T>
 double time_mask(Group& g, int precision, int reps, unsigned mask, lshom_status* st) {
   double ms[LSHOM_PASS_COUNT];
@@ -1787,15 +1800,21 @@ lshom_status autotune_group(Group& g, int precision, int reps, Schedule* best) {
     apply_schedule(g, s, precision);
     return f64 ? time_mask<double>(g, precision, reps, mask, &st) : time_mask<float>(g, precision, reps, mask, &st);
   };
+  bool tune_row = false, tune_col = false;
+  if (f64) scheduled_passes<double>(g, precision, &tune_row, &tune_col);
+  else scheduled_passes<float>(g, precision, &tune_row, &tune_col);
+  // both block sizes by name: 0 leaves the choice to the launch (pick_threads),
+  // which for most candidates is one of the two, and another one in a batch of
+  // another size
   // row pass: radix order of the last axis x rows per block
-  {
+  if (tune_row) {
     const unsigned mask = 1u << LSHOM_PASS_ROW;
     double best_t = 1e300;
     Schedule bs = cur;
     for (const FftPlan& pl : plan_candidates((int)g.N[last])) {
       for (int split = 0; split <= 1; ++split) {
         for (int r = 2; r <= 32; r += 2) {
-         for (int nt : {0, 256}) {
+         for (int nt : {128, 256}) {
           Schedule s = cur;
           s.plan[last] = pl;
           s.shape.rows_per_block = r;
@@ -1818,13 +1837,13 @@ lshom_status autotune_group(Group& g, int precision, int reps, Schedule* best) {
     cur.shape.threads_row = bs.shape.threads_row;
   }
   // axis-0 passes (inverse with the direction step, forward with the projection)
-  if (last != 0) {
+  if (last != 0 && tune_col) {
     const unsigned mask = (1u << LSHOM_PASS_AXIS0_INVERSE) | (1u << LSHOM_PASS_AXIS0_FORWARD);
     double best_t = 1e300;
     Schedule bs = cur;
     for (const FftPlan& pl : plan_candidates((int)g.N[0])) {
       for (int t0 = 1; t0 <= 16; t0 *= 2) {
-        for (int nt : {0, 256}) {
+        for (int nt : {128, 256}) {
           Schedule s = cur;
           s.plan[0] = pl;
           s.shape.tile0 = t0;
@@ -1844,7 +1863,7 @@ lshom_status autotune_group(Group& g, int precision, int reps, Schedule* best) {
     cur.shape.threads_col = bs.shape.threads_col;
   }
   // axis-1 passes (3-D)
-  if (g.d == 3) {
+  if (g.d == 3 && tune_col) {
     const unsigned mask = (1u << LSHOM_PASS_AXIS1_INVERSE) | (1u << LSHOM_PASS_AXIS1_FORWARD);
     double best_t = 1e300;
     Schedule bs = cur;
