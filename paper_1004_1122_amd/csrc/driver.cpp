@@ -965,9 +965,10 @@ int next_block_length(const Group& g, int per, const std::vector<double>& rr_pre
   return n;
 }
 
-// Iterations of a launch that holds whole solves: bounds the launch (about
-// 20 ms at 63^2), not the solve.
-constexpr int kResidentIters = 1024;
+// Blocks of iterations in a launch that holds whole solves: with the default
+// block of 16, 1008 iterations bound the launch (about 20 ms at 63^2), not the
+// solve.  (Odd, so that small blocks hand over at odd and even iterations.)
+constexpr int kResidentBlocks = 63;
 // Iterations queued before the host looks at the initial states: they cover
 // the time it needs to read them and to launch the first block (some 25 us; an
 // iteration takes 20 us or more).  A solve whose start is converged then skips
@@ -1326,7 +1327,7 @@ lshom_status solve_group(Group& g, const std::vector<DevState>& init, const lsho
   };
   if (use_resident(g, o.precision)) {
     // one launch until every problem has stopped, nothing to capture
-    s = run_blocks(g, 0, 0, kResidentIters, false, [&](int n) -> hipError_t {
+    s = run_blocks(g, 0, 0, kResidentBlocks * per, false, [&](int n) -> hipError_t {
       return enq_resident(g, get_bufs<double>(g), n, ffth, GATE_ACTIVE);
     });
   } else if (ffth) {
