@@ -73,6 +73,19 @@ inline int wgrad_splits(long long pixels) {
   return (int)(s < 64 ? s : 64);
 }
 
+// The kernel of a launch, by its shape.  Convolutions: the LDS patch of th
+// rows with the four waves in cw channel halves, or (th 0) wave tiles of 16 mt
+// pixels x 32 np channels straight from global memory.  Weight gradients:
+// columns per wave, and whether an image row is shorter than a lane's step.
+struct ConvVariant {
+  int th, cw, mt, np;
+};
+struct WgradVariant {
+  int columns;
+  bool small;
+};
+ConvVariant conv_variant(const ConvArgs& a);
+WgradVariant wgrad_variant(const WgradArgs& a, int splits);
 hipError_t launch_conv(const ConvArgs& a, hipStream_t s);
 hipError_t launch_wgrad(const WgradArgs& a, int splits, hipStream_t s);
 // grad[r][n] = sum_s partial[s][r][n] for r < rows (fixed order); row r = t cin

@@ -935,20 +935,14 @@ static hipError_t launch_conv3_tile(const ConvArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_conv(const ConvArgs& in, hipStream_t s) {
-  ConvArgs a = in;
-  a.wide_b = a.ldb % 8 == 0 && (reinterpret_cast<uintptr_t>(a.out_b) & 15u) == 0;
-  a.wide_f = a.ldf % 4 == 0 && (reinterpret_cast<uintptr_t>(a.out_f) & 15u) == 0;
-  a.wide_m = a.ldm % 8 == 0 && (reinterpret_cast<uintptr_t>(a.mask) & 15u) == 0;
-  a.fd_chunks = make_fastdiv((uint32_t)a.C0 / 8u);
+ConvVariant conv_variant(const ConvArgs& a) {
   if (a.mode == CM_CONV3 && a.Wo >= kConvTileSide) {
     // eight rows a block while two blocks fit a CU (the patch's two extra rows
     // weigh less: 64 -> 32 channels on 243^2 87 us, four rows 102 us), else
-    // four rows; wider layers (over 270 channels) read global memory per tap
-    if (conv3_tile_lds(8, a.C0) <= kConvTileLds8)
-      return a.N <= 32 ? launch_conv3_tile<8, 1>(a, s) : launch_conv3_tile<8, 2>(a, s);
-    if (conv3_tile_lds(4, a.C0) <= kConvTileLds4)
-      return a.N <= 32 ? launch_conv3_tile<4, 1>(a, s) : launch_conv3_tile<4, 2>(a, s);
+    // four rows (layers that wide have more than 32 output channels); from 296
+    // channels on layers read global memory per tap
+    if (conv3_tile_lds(8, a.C0) <= kConvTileLds8) return {8, a.N <= 32 ? 1 : 2, 0, 0};
+    if (conv3_tile_lds(4, a.C0) <= kConvTileLds4) return {4, 2, 0, 0};
   }
   // the largest wave tile that still gives two waves to most SIMDs; below
   // that a layer is bound by the length of its reduction, and narrow tiles
@@ -956,24 +950,49 @@ hipError_t launch_conv(const ConvArgs& in, hipStream_t s) {
   const long long M = (long long)a.B * a.Ho * a.Wo * (a.mode == CM_DOWN3_T ? 9 : 1);
   auto waves = [&](int mt, int np) { return ((M + 16 * mt - 1) / (16 * mt)) * ((a.Np + 32 * np - 1) / (32 * np)); };
   if (a.Np > 32) {
-    if (waves(4, 2) >= kConvWaves) return launch_conv_tile<4, 2, 2>(a, s);
-    if (waves(2, 2) >= kConvWaves) return launch_conv_tile<2, 2, 3>(a, s);
+    if (waves(4, 2) >= kConvWaves) return {0, 0, 4, 2};
+    if (waves(2, 2) >= kConvWaves) return {0, 0, 2, 2};
   } else if (waves(4, 1) >= kConvWaves) {
-    return launch_conv_tile<4, 1, 3>(a, s);
+    return {0, 0, 4, 1};
   }
-  if (waves(2, 1) >= kConvWaves) return launch_conv_tile<2, 1, 4>(a, s);
-  return launch_conv_tile<1, 1, 6>(a, s);
+  if (waves(2, 1) >= kConvWaves) return {0, 0, 2, 1};
+  return {0, 0, 1, 1};
+}
+
+hipError_t launch_conv(const ConvArgs& in, hipStream_t s) {
+  ConvArgs a = in;
+  a.wide_b = a.ldb % 8 == 0 && (reinterpret_cast<uintptr_t>(a.out_b) & 15u) == 0;
+  a.wide_f = a.ldf % 4 == 0 && (reinterpret_cast<uintptr_t>(a.out_f) & 15u) == 0;
+  a.wide_m = a.ldm % 8 == 0 && (reinterpret_cast<uintptr_t>(a.mask) & 15u) == 0;
+  a.fd_chunks = make_fastdiv((uint32_t)a.C0 / 8u);
+  const ConvVariant v = conv_variant(a);
+  if (v.th == 8) return v.cw == 1 ? launch_conv3_tile<8, 1>(a, s) : launch_conv3_tile<8, 2>(a, s);
+  if (v.th == 4) return launch_conv3_tile<4, 2>(a, s);
+  // (the narrower the tile, the more steps in flight)
+  if (v.np == 2) return v.mt == 4 ? launch_conv_tile<4, 2, 2>(a, s) : launch_conv_tile<2, 2, 3>(a, s);
+  if (v.mt == 4) return launch_conv_tile<4, 1, 3>(a, s);
+  return v.mt == 2 ? launch_conv_tile<2, 1, 4>(a, s) : launch_conv_tile<1, 1, 6>(a, s);
+}
+
+static unsigned wgrad_row_blocks(const WgradArgs& a) {
+  return (unsigned)((a.rows + kWgradRows * kWgradWaves - 1) / (kWgradRows * kWgradWaves));
+}
+
+WgradVariant wgrad_variant(const WgradArgs& a, int splits) {
+  // wide tiles read the input rows half as often, where they still give every
+  // second SIMD a wave
+  const long long wide_waves = (long long)wgrad_row_blocks(a) * kWgradWaves * ((a.Np + 63) / 64) * splits;
+  return {a.Np > 32 && wide_waves >= 512 ? 64 : 32, a.Wo < 8};
 }
 
 hipError_t launch_wgrad(const WgradArgs& a, int splits, hipStream_t s) {
-  const unsigned rb = (unsigned)((a.rows + kWgradRows * kWgradWaves - 1) / (kWgradRows * kWgradWaves));
-  // wide tiles read the input rows half as often, where they still give every
-  // second SIMD a wave
-  const int nb = a.Np > 32 && (long long)rb * kWgradWaves * ((a.Np + 63) / 64) * splits >= 512 ? 64 : 32;
+  const unsigned rb = wgrad_row_blocks(a);
+  const WgradVariant v = wgrad_variant(a, splits);
+  const int nb = v.columns;
   const dim3 grid(rb, (unsigned)((a.Np + nb - 1) / nb), (unsigned)splits);
   const int kind = a.mode != CM_CONV3 ? WG_PLAIN : (a.up == 3 ? WG_UP3 : WG_CONV3);
   auto launch = [&](auto NB, auto KIND) {
-    if (a.Wo < 8) hipLaunchKernelGGL((wgrad_kernel<NB(), KIND(), true>), grid, dim3(64 * kWgradWaves), 0, s, a);
+    if (v.small) hipLaunchKernelGGL((wgrad_kernel<NB(), KIND(), true>), grid, dim3(64 * kWgradWaves), 0, s, a);
     else hipLaunchKernelGGL((wgrad_kernel<NB(), KIND(), false>), grid, dim3(64 * kWgradWaves), 0, s, a);
   };
   auto launch_kind = [&](auto NB) {
