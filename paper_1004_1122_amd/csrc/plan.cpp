@@ -98,25 +98,32 @@ PassShape default_shape(int d, const int64_t* N, const FftPlan* plans, int elem_
   // it; in the transposed layout each global access covers rows_per_block
   // contiguous elements, and neighbouring blocks on one XCD share the lines:
   // four rows (900^2 FP64: six rows 35 us, four 28 us, two 26 us; three such
-  // problems a solve 4.75, 4.47 and 4.56 ms).
+  // problems a solve 4.75, 4.47 and 4.56 ms; FP32, six / four / two rows: 24 /
+  // 20 / 20 us, four problems 45 / 38 / 48 us, 1000^2 25 / 21 / 21 us).
   // 3-D grids below 2^21 nodes leave a full-size block (three components, two
   // thousand points) too much serial work for the blocks there are: one
   // component and about a thousand points then (row pass FP64, 105 x 135 x 77
-  // 39 -> 29 us, 60^3 21 -> 16 us; 140^3 the other way, 63 -> 69 us)
+  // 39 -> 29 us, 60^3 21 -> 16 us; 140^3 the other way, 63 -> 69 us), and not
+  // below 256 points for the sake of a single small image's block count: its
+  // pass takes what a launch takes (FP64, 20^3: 9.3 us with 20 points a block,
+  // 9.1 with 260, 9.9 with 520), while a batch pays for idle threads (128 of
+  // 20^3: 190 us with 20 points, 28 with 260; of 30^3: 155 us with 90, 73 with 270)
   {
     const int cap = plan_batch_cap(plans[last], kMaxThreads);
     s.row_split = (allow_split && (transposed || nrows * n_last < (1ll << 21))) ? 1 : 0;
     const long long enough = s.row_split ? 1024 : 2048;
     const int comps = s.row_split ? 1 : d;
     const int target = transposed ? 4 : 64;
+    const long long at_least = !transposed && s.row_split ? 256 : 0;
+    auto points = [&](int r) { return (long long)comps * (r / 2) * n_last; };
     int best = 2;
-    for (int r = 2; r <= target; r += 2) {
-      if ((long long)comps * (r / 2) * n_last > cap) break;
+    for (int r = 2; r <= target && r <= nrows + 1; r += 2) {
+      if (points(r) > cap) break;
       if (row_lds_bytes(n_last, r, comps, elem_bytes, n_phases, nullptr) > lds_budget) break;
       best = r;
-      if (!transposed && (long long)comps * (r / 2) * n_last >= enough) break;
+      if (!transposed && points(r) >= enough) break;
     }
-    while (best > 2 && ceil_div(nrows, best) < min_blocks) best -= 2;
+    while (best > 2 && ceil_div(nrows, best) < min_blocks && points(best - 2) >= at_least) best -= 2;
     s.rows_per_block = best;
   }
   // strided passes: contiguous columns need no tile (transposed); in the
