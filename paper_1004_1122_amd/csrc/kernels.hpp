@@ -522,6 +522,9 @@ bool resident_fits(const int64_t* N, size_t lds_limit);
 hipError_t launch_resident(const ResidentArgs& a, bool basic, hipStream_t s);
 
 // Host launchers (passes.hip).
+// Threads of a block pass whose schedule leaves them open (0): points and LDS
+// bytes of a block, blocks of the launch, bytes of a complex element.
+int pick_threads(int points, const FftPlan& plan, size_t lds, long long blocks, int elem_bytes);
 template <typename T> hipError_t launch_row(const RowArgs<T>& a, hipStream_t s);
 template <typename T> hipError_t launch_col(const ColArgs<T>& a, hipStream_t s);
 template <typename T> hipError_t launch_update(const UpdArgs<T>& a, hipStream_t s);

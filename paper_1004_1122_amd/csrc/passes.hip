@@ -1470,7 +1470,10 @@ long long update_blocks(long long n) {
 // - where the launch has so few blocks that the chip has room for them and a
 //   block has more points than two waves have lanes (per iteration, FP64:
 //   360^2 51 -> 47 us, 625^2 80 -> 65 us, 60^3 85 -> 74 us; five problems of
-//   150^2 1.13 -> 1.10 ms, but twelve 1.32 -> 1.55 ms);
+//   150^2 1.13 -> 1.10 ms, but twelve 1.32 -> 1.55 ms).  A CU holds four such
+//   blocks, of the FP64 kernels with the wide primes three (axis-0 inverse
+//   pass, 255^2, six problems, 768 blocks 14.6 -> 13.4 us, eight, 1024 blocks
+//   14.7 -> 19.4 us; 119^2, sixteen, 960 blocks 11.8 -> 16.8 us);
 // - where 160 or more butterflies of a heavy radix would give two waves a
 //   second round that leaves one of them idle, and the blocks a CU can hold
 //   are too few to fill in (twenty-four problems of 500^2 FP64, 200
@@ -1478,12 +1481,13 @@ long long update_blocks(long long n) {
 // With more blocks two waves are the better (32 problems of 243^2 FP32, 3.9 KB
 // a block: 15.2 us, with four 17.5 us).  The sums do not depend on the choice
 // (block_sums_shared), so a batch still reproduces single solves bit for bit.
-static int pick_threads(int points, const FftPlan& plan, size_t lds, long long blocks) {
+int pick_threads(int points, const FftPlan& plan, size_t lds, long long blocks, int elem_bytes) {
   if (points > plan_batch_cap(plan, 128)) return 256;
   int heavy = 0;
   for (int s = 0; s < plan.nstages; ++s)
     if (plan.radix[s] >= 5) heavy = std::max(heavy, points / plan.radix[s]);
-  if (points > 128 && blocks <= 1024) return 256;
+  const long long room = elem_bytes == 16 && plan_radix_set(plan) == RADIX_WIDE ? 768 : 1024;
+  if (points > 128 && blocks <= room) return 256;
   return heavy >= 160 && 7 * lds > 160 * 1024 ? 256 : 128;
 }
 
@@ -1595,7 +1599,7 @@ hipError_t launch_row(const RowArgs<T>& a, hipStream_t s) {
   const int comps = a.split ? 1 : a.d;
   const size_t lds = row_lds_bytes(a.n, a.rows_per_block, comps, (int)sizeof(cx<T>), a.n_phases, nullptr);
   const long long nb = row_blocks(a);
-  const int nt = a.nt ? a.nt : pick_threads(comps * (a.rows_per_block / 2) * a.n, a.plan, lds, nb * nprob_of(a.bt));
+  const int nt = a.nt ? a.nt : pick_threads(comps * (a.rows_per_block / 2) * a.n, a.plan, lds, nb * nprob_of(a.bt), (int)sizeof(cx<T>));
   switch (plan_radix_set(a.plan)) {
     case RADIX_POW3: launch_row_rs<T, RADIX_POW3>(a, lds, nb, nt, s); break;
     case RADIX_POW2: launch_row_rs<T, RADIX_POW2>(a, lds, nb, nt, s); break;
@@ -1610,7 +1614,7 @@ hipError_t launch_col(const ColArgs<T>& a, hipStream_t s) {
   if (w2_col(a) && !a.pipe && (a.mode == COL_INV_C || a.mode == COL_FWD_PROJ)) return launch_w2_col(a, s);
   const size_t lds = col_lds_bytes(a.L, a.tile, a.d, (int)sizeof(cx<T>), nullptr);
   const long long nb = col_blocks(a);
-  const int nt = a.nt ? a.nt : pick_threads(a.d * a.tile * a.L, a.plan, lds, nb * nprob_of(a.bt));
+  const int nt = a.nt ? a.nt : pick_threads(a.d * a.tile * a.L, a.plan, lds, nb * nprob_of(a.bt), (int)sizeof(cx<T>));
   switch (plan_radix_set(a.plan)) {
     case RADIX_POW3: launch_col_rs<T, RADIX_POW3>(a, lds, nb, nt, s); break;
     case RADIX_POW2: launch_col_rs<T, RADIX_POW2>(a, lds, nb, nt, s); break;
