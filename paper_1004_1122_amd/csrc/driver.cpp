@@ -740,17 +740,25 @@ hipError_t enq_true_residual(Group& g, const Bufs<T>& b, const cx<T>* x, const d
 // coordinate: x <- -(1/l0) P dL (E + u(x)), i.e. e^(m+1) = e0 - B e^(m); the
 // step x_new - x (the residual of e^(m)) is reduced for the tests, which the
 // next step takes first (with the equilibrium sums: a launch after each step).
+// In launches of many blocks every one of them would sum the step's partials
+// again, which costs more than the launch: 256 problems of 17 x 500, 64256
+// blocks, 31.5 ms a solve with the test in the pass and 29.0 with a launch, 256
+// of 17 x 255, 32768 blocks, 18.3 and 17.3; 900 of 51 x 51, 23400 blocks, 26.3
+// and 25.7; eight of 255^2, 1024 blocks, 3.09 and 3.11.
+constexpr long long kRideBlocks = 8192;
 hipError_t enq_ffth_iteration(Group& g, const Bufs<double>& b, int gate) {
   hipError_t e;
   cx<double>* x = b.v[0];
+  const int rows = g.live_rows > 0 ? g.live_rows : g.nprob;
+  const bool ride = !g.eq && col0_block_count(g, b) * rows <= kRideBlocks;
   g.in_cg = true;
-  g.basic_step = !g.eq;
+  g.basic_step = ride;
   e = enq_apply_spec<double>(g, b, x, nullptr, nullptr, nullptr, x, x, 0.0, -1.0, 3, PART_RR0, gate,
                              g.eq ? 1 : 0);
   g.in_cg = false;
   g.basic_step = false;
-  if (e != hipSuccess || !g.eq) return e;
-  return enq_finalize(g, FZ_FFTH, 0, gate, 1);
+  if (e != hipSuccess || ride) return e;
+  return enq_finalize(g, FZ_FFTH, 0, gate, g.eq ? 1 : 0);
 }
 
 // r0 for x0 = E: r0 = -(1/l0) P dL E.
