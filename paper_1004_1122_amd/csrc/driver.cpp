@@ -684,11 +684,13 @@ hipError_t enq_cg_iteration(Group& g, const Bufs<T>& b, int gate) {
 // five; 63 x 70 at 1e5: none and one); with other inputs it is the other way.
 // So mixed solves stay on the passes and converge where they always did (in
 // FP64 such an image takes less time: 63^2 0.53 ms, mixed in one block 0.70).
-bool resident_grid(const Group& g, int precision) {
-  return precision == LSHOM_PRECISION_FP64 && g.d == 2 && !g.tensor && !g.aniso && resident_fits(g.N, lds_limit_of(g));
+bool use_resident(const Group& g, int precision) {
+  return precision == LSHOM_PRECISION_FP64 && g.d == 2 && !g.eq && !g.tensor && !g.aniso && !g.timer &&
+         resident_fits(g.N, lds_limit_of(g));
 }
-bool use_resident(const Group& g, int precision) { return resident_grid(g, precision) && !g.eq && !g.timer; }
 
+// (The default radices, whatever the schedule: the autotuner's are the fastest
+// of the block passes, where a stage costs less than here.)
 hipError_t enq_resident(Group& g, const Bufs<double>& b, int iters, bool basic, int gate) {
   ResidentArgs a{};
   a.N0 = (int)g.N[0];
@@ -696,7 +698,7 @@ hipError_t enq_resident(Group& g, const Bufs<double>& b, int iters, bool basic, 
   a.h = g.h;
   a.iters = iters;
   for (int t = 0; t < 2; ++t) {
-    a.plan[t] = b.plan[t];
+    a.plan[t] = default_plan((int)g.N[t]);
     a.tw[t] = b.tw[t];
     a.cinv[t] = g.cell_inv[t];
   }
@@ -1709,9 +1711,10 @@ lshom_status time_passes(Group& g, int precision, int reps, double* ms_out, doub
 // ---------------------------------------------------------------------------
 // Autotuner: each pass kind is tuned on its own (its radix order and launch
 // shape change only its own kernels), timing real launches on the group.
-// Passes whose launches no schedule changes (wave passes) and grids whose plain
-// solves run no passes (one block per image) keep the schedule they have: their
-// candidates would differ by noise only.
+// What is timed are the passes of pipelined CG, histories, the equilibrium norm
+// and pass timing where plain solves run the 3-D wave passes or one block per
+// image.  2-D passes whose launches no schedule changes (wave passes) keep the
+// schedule they have: their candidates would differ by noise only.
 // ---------------------------------------------------------------------------
 
 namespace {
@@ -1759,14 +1762,12 @@ std::vector<FftPlan> plan_candidates(int n) {
   return out;
 }
 
-// Whether CG solves of the group launch the row pass and the axis-0 passes as
-// the schedule says.
+// Whether the timed row pass and axis-0 passes are launched as the schedule says.
 template <typename T>
-void scheduled_passes(Group& g, int precision, bool* row, bool* col) {
+void scheduled_passes(Group& g, bool* row, bool* col) {
   const Bufs<T> b = get_bufs<T>(g);
-  const bool passes = !(g.w3ok && !g.aniso && !g.tensor) && !resident_grid(g, precision);
-  *row = passes && !w2_row(row_args(g, b));
-  *col = passes && !w2_col(col0_args(g, b));
+  *row = !w2_row(row_args(g, b));
+  *col = !w2_col(col0_args(g, b));
 }
 
 template <typename T>
@@ -1810,8 +1811,8 @@ lshom_status autotune_group(Group& g, int precision, int reps, Schedule* best) {
     return f64 ? time_mask<double>(g, precision, reps, mask, &st) : time_mask<float>(g, precision, reps, mask, &st);
   };
   bool tune_row = false, tune_col = false;
-  if (f64) scheduled_passes<double>(g, precision, &tune_row, &tune_col);
-  else scheduled_passes<float>(g, precision, &tune_row, &tune_col);
+  if (f64) scheduled_passes<double>(g, &tune_row, &tune_col);
+  else scheduled_passes<float>(g, &tune_row, &tune_col);
   // both block sizes by name: 0 leaves the choice to the launch (pick_threads),
   // which for most candidates is one of the two, and another one in a batch of
   // another size
