@@ -24,7 +24,9 @@
  *  - Device pointers (suffix _dev) are HIP device memory owned by the caller;
  *    host pointers (suffix _host or plain arrays) are read during the call.
  *  - The library never allocates device memory: the caller provides one
- *    workspace (lshom_workspace_size / lshom_set_workspace).
+ *    workspace (lshom_workspace_size / lshom_set_workspace).  A context holds
+ *    some pinned host memory (the states of 64 problems, or of the largest
+ *    batch that lshom_batch_workspace_size was asked for).
  *  - Calls are blocking: work is queued on the context's stream after the
  *    caller's stream and the call returns when it has finished.
  *  - Errors are reported by status codes; no C++ exception crosses the ABI.
@@ -71,7 +73,9 @@ typedef struct lshom_solve_opts {
   int32_t precision;     /* LSHOM_PRECISION_FP64 */
   int32_t refresh_every; /* 50: mixed only, FP64 refresh at least this often */
   double refresh_drop;   /* 0.01: mixed only, refresh when ||r|| fell by this factor */
-  int32_t graph_block;   /* 16: iterations per captured HIP graph launch (0: no graph) */
+  int32_t graph_block;   /* 16: iterations per captured HIP graph launch (0: no graph); where a
+                            whole solve runs in one block (see lshom_schedule), 63 times as many
+                            per launch (0: 504) */
   int32_t true_residual; /* 1: recompute b - A x in FP64 after the loop (and eta_e, odd N) */
   int32_t method;        /* LSHOM_METHOD_CG; FFTH, BICG and PIPECG: FP64 only, no x0; BICG and
                             PIPECG: single solves, residual norm, no history, workspace from
@@ -83,7 +87,9 @@ typedef struct lshom_solve_opts {
    * [2m], [2m + 1] for m < history_len.  CG: iterates x_0 .. x_iterations
    * (eta_r from the recursive residual); FFTH: e^0 .. e^(iterations - 1),
    * whose residual is the step to the next iterate.  Entries past the last
-   * iterate are left untouched.
+   * iterate are left untouched.  A solve with a history, or with the
+   * equilibrium norm, runs the block passes on the grids whose plain solves run
+   * 3-D wave passes or one block per image: the same iterates to rounding.
    */
   double* history_dev;
   int32_t history_len;   /* 0 */
@@ -333,12 +339,27 @@ lshom_status lshom_solve_batched(lshom_ctx* ctx, int32_t n, const lshom_problem*
 
 /*
  * Launch schedule of one grid at one precision: the radix order of each
- * axis's FFT (product = N[a]; radices 2..9) and the pass shapes (rows of the
- * last axis per row-pass block, an even number; whether a row-pass block
- * holds one component (row_split = 1) or all d; column tiles of the axis-0
- * and axis-1 passes; block sizes of the row and axis passes, 128 or 256
- * threads, 0 for the smallest that holds the batch).  Results do not depend on the schedule beyond
- * floating-point rounding.
+ * axis's FFT (product = N[a]; radices 2..9, 11, 13, 17) and the pass shapes
+ * (rows of the last axis per row-pass block, an even number; whether a row-pass
+ * block holds one component (row_split = 1) or all d; column tiles of the
+ * axis-0 and axis-1 passes; block sizes of the row and axis passes, 128 or 256
+ * threads, 0 to leave the size to each launch, which takes 256 where 128 cannot
+ * hold the block's transforms or the launch has few blocks).  Results do not
+ * depend on the schedule beyond floating-point rounding, and not at all on the
+ * block sizes.
+ *
+ * A schedule shapes the block passes.  It has no effect
+ *  - on the wave passes: with scalar phases and an isotropic reference, along
+ *    2-D axes of 81, 243 and 729 nodes (whatever the other axis is), and in CG,
+ *    BiCG and basic-scheme solves and applies on 3-D grids of 27, 81 and 243
+ *    nodes per axis;
+ *  - on FP64 CG and basic-scheme solves of 2-D images that run whole in one
+ *    block: up to about 67 x 67 nodes (axes with the factors 2, 3, 5 and 7;
+ *    N[0] (N[1] / 2 + 1) and (N[0] + 1) / 2 N[1] at most 2304), scalar phases and
+ *    isotropic reference.
+ * Pipelined CG and solves with a history or the equilibrium norm run the block
+ * passes on such 3-D grids and small images, and there it counts (and with pass
+ * timing on, for small images).
  */
 typedef struct lshom_schedule {
   int32_t d;
@@ -363,7 +384,7 @@ lshom_status lshom_get_schedule(lshom_ctx* ctx, int precision, lshom_schedule* o
 /*
  * Register a schedule for its grid and precision (used by later solves of
  * that grid, single or batched; applied at once to the current problem when
- * the grid matches).  INVALID_ARG if it does not factor N or does not fit the
+ * the grid matches; see lshom_schedule for where it has an effect).  INVALID_ARG if it does not factor N or does not fit the
  * FFT batch or LDS limits.
  */
 lshom_status lshom_set_schedule(lshom_ctx* ctx, const lshom_schedule* s);
@@ -407,8 +428,9 @@ lshom_status lshom_load_schedules(lshom_ctx* ctx, const char* path);
  * Device time of each pass kernel of one CG iteration (Sec. 2.3: the apply of
  * Eq. (16) plus the CG vector updates) for the current problem at `precision`:
  * every kernel is launched `reps` times back to back on the context stream,
- * with the same launch shape and buffers as in lshom_solve, between two HIP
- * events.  ms_out[LSHOM_PASS_COUNT] receives the average milliseconds per
+ * with the same launch shape and buffers as in lshom_solve (on grids whose FP64
+ * solves run whole in one block: as in a solve with pass timing), between two
+ * HIP events.  ms_out[LSHOM_PASS_COUNT] receives the average milliseconds per
  * launch (0 for passes a 2-D problem does not have); bytes_out (may be NULL)
  * the minimum HBM bytes each launch must move (its algorithmic traffic).
  * Overwrites the solver's internal vectors: call it between solves.
@@ -425,7 +447,9 @@ lshom_status lshom_time_passes(lshom_ctx* ctx, int precision, int reps, double* 
  * the algorithmic HBM bytes of the work those launches did (the per-problem
  * bytes of lshom_time_passes times the CG iterations the problems actually
  * advanced; launches for problems that had already stopped count zero
- * bytes).  Enabling (or disabling) resets the sums.  Arrays hold
+ * bytes).  FP64 solves of images that otherwise run whole in one block run the
+ * passes while timing is enabled: the same iterates to rounding, in another
+ * time.  Enabling (or disabling) resets the sums.  Arrays hold
  * LSHOM_PASS_COUNT entries; any may be NULL.
  */
 lshom_status lshom_set_pass_timing(lshom_ctx* ctx, int enable);

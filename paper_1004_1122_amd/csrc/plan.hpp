@@ -9,11 +9,11 @@
 
 namespace lshom {
 
-// True if n factors over {2, 3, 5, 7}.
+// True if n factors over {2, 3, 5, 7, 11, 13, 17}.
 bool fft_size_ok(int64_t n);
 
-// Default radix schedule for an axis of n points: radix 9 first, then
-// 8, 7, 5, 6, 4, 3, 2 greedily.  An explicit schedule (autotuner) may replace it.
+// Default radix schedule for an axis of n points: 17, 13, 11, 9, 8, 7, 5, 6, 4,
+// 3, 2 greedily.  An explicit schedule (autotuner) may replace it.
 FftPlan default_plan(int n);
 
 // Validates a caller-given schedule; fills plan on success.
@@ -28,12 +28,13 @@ struct PassShape {
   int tile0;             // axis-0 pass tile
   int tile1;             // axis-1 pass tile (3-D)
   int row_split;         // row pass: one component per block
-  int threads_row;       // block size of the row pass (0: smallest that holds the batch)
+  int threads_row;       // block size of the row pass (0: by the launch, pick_threads)
   int threads_col;       // block size of the axis passes (0: as above)
 };
 
 // Default shapes within the FFT batch limit (256 threads) and lds_budget
-// bytes of LDS, reduced while a pass would have fewer than min_blocks blocks.
+// bytes of LDS, reduced while a pass would have fewer than min_blocks blocks (3-D
+// row blocks of one component: not below 256 points).
 // `transposed`: 2-D spectral arrays stored [k1][k0] (columns contiguous).
 // `allow_split`: the row pass may hold one component per block (not for
 // tensor phases, whose polarisation couples the components of a node).

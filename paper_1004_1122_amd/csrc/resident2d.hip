@@ -6,8 +6,9 @@
 // A small image is bound by latency: of the 28 us of a 63^2 FP64 iteration on
 // four launches about half is launches, waits for the previous launch's sums
 // and memory latency, on a chip that is otherwise empty.  Here an iteration
-// has block barriers only, and is bound by the issue rate of one CU (an FP32
-// build took the same time).  63^2: 27 -> 18 us per iteration (1024
+// has block barriers only: its two waves per SIMD issue an instruction in 27% of
+// their cycles and wait, for LDS and at barriers, in 55% (counters of a 63^2
+// solve; an FP32 build took the same time).  63^2: 27 -> 18 us per iteration (1024
 // threads spilled 300 registers; x, r and p in global memory 23 us; one copy
 // of the transform code in place of four, with the inverse ones as transforms
 // of conjugates, 22 us).  Solves: 63^2, 21 iterations, 0.73 -> 0.55 ms; 64 of
